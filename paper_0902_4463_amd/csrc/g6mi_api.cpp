@@ -113,7 +113,7 @@ struct Handle {
   PinBuf h_i, h_out;
 
   // work buffers
-  DevBuf d_part, d_nnr2, d_nnslot, d_nbcount, d_nblist, d_flags, d_ovf;
+  DevBuf d_part, d_nnslot, d_nbcount, d_nblist, d_flags, d_ovf;
   // neighbour counters of the fused path: all zero between calculations
   // (each reduction clears the rows it used); nbwork_ok is false until a
   // new buffer has been cleared or after a calculation that did not reach
@@ -417,7 +417,7 @@ int ensure_spatial(Handle &h, int nj, int ni) {
 // Work buffers of one single-system calculation.
 struct CalcBufs {
   void *pred = nullptr;                    // predicted j-records (not with the fused kernel)
-  double *part = nullptr, *nnr2 = nullptr; // split partials
+  double *part = nullptr;                  // split partials
   int *nnslot = nullptr;
   int *nbcount = nullptr, *nblist = nullptr;
   int *flags = nullptr, *ovf = nullptr;    // status words, overflow queue
@@ -433,8 +433,7 @@ size_t calc_bytes(int prec, bool fused, int nj, int ni, int nsplit) {
   size_t b = 0;
   auto add = [&](size_t x) { b += round_up(x, 256); };
   add(fused ? 0 : std::max<size_t>(1, nj) * pred_record_bytes(prec));
-  add(ns * 7 * n * sizeof(double));
-  add(ns * n * sizeof(double));
+  add(ns * n * kPartDoubles * sizeof(double));
   add(ns * n * sizeof(int));
   add(n * sizeof(int));
   add(n * kNbMax * sizeof(int));
@@ -455,8 +454,7 @@ CalcBufs carve_bufs(void *base, int prec, bool fused, int nj, int ni, int nsplit
   };
   CalcBufs c;
   c.pred = take(fused ? 0 : std::max<size_t>(1, nj) * pred_record_bytes(prec));
-  c.part = static_cast<double *>(take(ns * 7 * n * sizeof(double)));
-  c.nnr2 = static_cast<double *>(take(ns * n * sizeof(double)));
+  c.part = static_cast<double *>(take(ns * n * kPartDoubles * sizeof(double)));
   c.nnslot = static_cast<int *>(take(ns * n * sizeof(int)));
   c.nbcount = static_cast<int *>(take(n * sizeof(int)));
   c.nblist = static_cast<int *>(take(n * kNbMax * sizeof(int)));
@@ -472,8 +470,7 @@ CalcBufs carve_bufs(void *base, int prec, bool fused, int nj, int ni, int nsplit
 int handle_bufs(Handle &h, bool fused, int nj, int ni, int nsplit, CalcBufs &c) {
   const size_t n = static_cast<size_t>(std::max(ni, 1));
   if (!fused) HIPCHK(&h, ensure(h.d_pred, std::max<size_t>(1, nj) * pred_record_bytes(h.prec)));
-  HIPCHK(&h, ensure(h.d_part, static_cast<size_t>(nsplit) * 7 * n * sizeof(double)));
-  HIPCHK(&h, ensure(h.d_nnr2, static_cast<size_t>(nsplit) * n * sizeof(double)));
+  HIPCHK(&h, ensure(h.d_part, static_cast<size_t>(nsplit) * n * kPartDoubles * sizeof(double)));
   HIPCHK(&h, ensure(h.d_nnslot, static_cast<size_t>(nsplit) * n * sizeof(int)));
   HIPCHK(&h, ensure(h.d_nbcount, n * sizeof(int)));
   HIPCHK(&h, ensure(h.d_nblist, n * kNbMax * sizeof(int)));
@@ -481,7 +478,6 @@ int handle_bufs(Handle &h, bool fused, int nj, int ni, int nsplit, CalcBufs &c) 
   HIPCHK(&h, ensure(h.d_ovf, 2 * n * sizeof(int)));
   c.pred = fused ? nullptr : h.d_pred.p;
   c.part = static_cast<double *>(h.d_part.p);
-  c.nnr2 = static_cast<double *>(h.d_nnr2.p);
   c.nnslot = static_cast<int *>(h.d_nnslot.p);
   c.nbcount = static_cast<int *>(h.d_nbcount.p);
   c.nblist = static_cast<int *>(h.d_nblist.p);
@@ -569,7 +565,6 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
   a.ipw = ipw;
   a.log2ipw = ilog2(ipw);
   a.part = c.part;
-  a.nn_r2 = c.nnr2;
   a.nn_slot = c.nnslot;
   a.nb_count = c.nbcount;
   a.nb_slot = c.nblist;
@@ -581,7 +576,7 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
     HIPCHK(&h, launch_force(h.prec, h.nbl, a, nsplit, s));
   }
   if (ev) HIPCHK(&h, hipEventRecord(ev[2], s));
-  HIPCHK(&h, launch_reduce(nsplit, ni, spatial ? h.sp.iperm : nullptr, a.part, a.nn_r2, a.nn_slot, h.jm.index,
+  HIPCHK(&h, launch_reduce(nsplit, ni, spatial ? h.sp.iperm : nullptr, a.part, a.nn_slot, h.jm.index,
                            a.nb_count, a.nb_slot, h.nbl, d_acc, d_jerk, d_pot, d_nnb, d_r2nn, status, c.ovf, s,
                            c.nbwork));
   // the reduction clears the fused counters again (without lists nothing was counted)
@@ -735,7 +730,7 @@ int lasthalf_impl(int id, int nj, int ni, const int *index, double eps2, double 
 // Partial sums of a batch: at most this many bytes (7 sums, r^2 and slot per
 // i-particle and j-split); the j-split cap is lowered to fit.
 constexpr size_t kBatchPartialBudget = size_t(4) << 30;
-constexpr size_t kPartialEntryBytes = 7 * sizeof(double) + sizeof(double) + sizeof(int);
+constexpr size_t kPartialEntryBytes = kPartDoubles * sizeof(double) + sizeof(int);
 constexpr int kBatchMaxClusters = 1 << 20;
 
 // Persistent workgroups per CU that the batch kernel's registers allow: the
@@ -767,8 +762,7 @@ std::vector<uint64_t> graph_key(const Handle &h, const BatchArgs &b, int grid, h
           static_cast<uint64_t>(b.item_cap), static_cast<uint64_t>(b.tune.item_work),
           static_cast<uint64_t>(b.tune.wide_min), static_cast<uint64_t>(b.tune.max_split),
           u(b.jm.t), static_cast<uint64_t>(b.jm.cap), u(b.fa.xi), u(b.fa.vi), u(b.fa.h2),
-          u(b.fa.islot), u(b.fa.nb_count), u(b.fa.nb_slot), u(b.part), u(b.nn_r2), u(b.nn_slot),
-          static_cast<uint64_t>(b.pcap), u(b.ib_cl), static_cast<uint64_t>(b.nbl), u(b.acc),
+          u(b.fa.islot), u(b.fa.nb_count), u(b.fa.nb_slot), u(b.part), u(b.nn_slot), u(b.ib_cl), static_cast<uint64_t>(b.nbl), u(b.acc),
           u(b.jerk), u(b.pot), u(b.r2nn), u(b.nnb), u(b.status), u(b.ovf_list), u(b.ovf_tag),
           static_cast<uint64_t>(h.prec), static_cast<uint64_t>(grid), u(s)};
 }
@@ -830,8 +824,7 @@ int prepare_batch(Handle &h, int ncl, const g6mi_cluster *d_cl, int ni_total, in
   HIPCHK(&h, ensure(h.d_items, item_cap * sizeof(int)));
   HIPCHK(&h, ensure(h.d_bwork, sizeof(BatchWork)));
   HIPCHK(&h, ensure(h.d_ibcl, n * sizeof(int)));
-  HIPCHK(&h, ensure(h.d_part, 7 * pcap * sizeof(double)));
-  HIPCHK(&h, ensure(h.d_nnr2, pcap * sizeof(double)));
+  HIPCHK(&h, ensure(h.d_part, pcap * kPartDoubles * sizeof(double)));
   HIPCHK(&h, ensure(h.d_nnslot, pcap * sizeof(int)));
   HIPCHK(&h, ensure(h.d_nbcount, n * sizeof(int)));
   HIPCHK(&h, ensure(h.d_nblist, n * kNbMax * sizeof(int)));
@@ -859,9 +852,7 @@ int prepare_batch(Handle &h, int ncl, const g6mi_cluster *d_cl, int ni_total, in
   b.fa.nb_count = static_cast<int *>(h.d_nbcount.p);
   b.fa.nb_slot = static_cast<int *>(h.d_nblist.p);
   b.part = static_cast<double *>(h.d_part.p);
-  b.nn_r2 = static_cast<double *>(h.d_nnr2.p);
   b.nn_slot = static_cast<int *>(h.d_nnslot.p);
-  b.pcap = pcap;
   b.ib_cl = static_cast<int *>(h.d_ibcl.p);
   b.nbl = h.nbl ? 1 : 0;
   b.acc = d_acc;
@@ -1024,7 +1015,7 @@ G6MI_API int g6_close(int id) {
   for (DevBuf *b : {&h->hs.d_ctl, &h->hs.d_state, &h->hs.d_block}) b->release();
   h->hs.h_ctl.release();
   for (DevBuf *b : {&h->d_jm, &h->d_pred, &h->d_stage, &h->d_i, &h->d_out, &h->d_part,
-                    &h->d_nnr2, &h->d_nnslot, &h->d_nbcount, &h->d_nblist, &h->d_flags,
+                    &h->d_nnslot, &h->d_nbcount, &h->d_nblist, &h->d_flags,
                     &h->d_ovf, &h->d_cl, &h->d_plan, &h->d_items, &h->d_bwork, &h->d_ibcl, &h->d_sp})
     b->release();
   for (PinBuf *b : {&h->h_stage, &h->h_i, &h->h_out, &h->h_cl}) b->release();

@@ -227,18 +227,6 @@ __global__ __launch_bounds__(256) void batch_plan_kernel(BatchArgs b) {
 
 // ------------------------------------------------------ persistent kernel
 
-__device__ __forceinline__ void store_partial(const BatchArgs &b, size_t e, const Totals &t, double best,
-                                              int bslot) {
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    b.part[d * b.pcap + e] = t.acc[d];
-    b.part[(3 + d) * b.pcap + e] = t.jrk[d];
-  }
-  b.part[6 * b.pcap + e] = t.pot;
-  b.nn_r2[e] = best;
-  b.nn_slot[e] = bslot;
-}
-
 // Persistent workgroups: workgroup g starts with item g, then takes the
 // next item from its queue until the items run out (every wave reaches the
 // exit: items are finite and each workgroup takes one item per round).  The
@@ -249,7 +237,7 @@ __device__ __forceinline__ void store_partial(const BatchArgs &b, size_t e, cons
 // no atomic at all: hundreds of workgroups incrementing one counter at once
 // queue up behind each other.
 // Partial entry of i-particle il (cluster row) in split s: pbase + s * ni +
-// il, component-major over pcap entries.
+// il.
 // WIDE = false: the narrow-only kernel, for batches whose plan cannot make a
 // wide block (the host launches it only when tune.wide_min > ni_total); its
 // registers fit four waves per SIMD.
@@ -296,8 +284,8 @@ __global__ __launch_bounds__(kWG, WIDE ? wide_waves<PREC>() : kNarrowWaves) void
         w.template tile<PREC == G6MI_PREC_DS, true>(tile, jbase, cnt, eps2, b.fa.nb_count, b.fa.nb_slot);
         w.resolve(tile, jbase); // while the tile is still in LDS
       }
-      if (w.v0) store_partial(b, e0 + il0, w.t0, static_cast<double>(w.ebest0), w.eslot0);
-      if (w.v1) store_partial(b, e0 + il1, w.t1, static_cast<double>(w.ebest1), w.eslot1);
+      if (w.v0) store_part(b.part, b.nn_slot, e0 + il0, w.t0, static_cast<double>(w.ebest0), w.eslot0);
+      if (w.v1) store_part(b.part, b.nn_slot, e0 + il1, w.t1, static_cast<double>(w.ebest1), w.eslot1);
     } else {
       const int ipw = p.ipw;
       const int lil = tid & (ipw - 1);
@@ -316,7 +304,7 @@ __global__ __launch_bounds__(kWG, WIDE ? wide_waves<PREC>() : kNarrowWaves) void
       double bestd;
       int bslot;
       n.lane_sum(reinterpret_cast<double *>(lds), tid, lil, ipw, bestd, bslot);
-      if (n.sub == 0 && n.valid) store_partial(b, e0 + il, n.t, bestd, bslot);
+      if (n.sub == 0 && n.valid) store_part(b.part, b.nn_slot, e0 + il, n.t, bestd, bslot);
     }
     if (static_cast<int>(gridDim.x) >= nitems) break; // no second round
     __syncthreads(); // the item is done with the LDS and s_item
@@ -334,17 +322,17 @@ __global__ __launch_bounds__(kWG, WIDE ? wide_waves<PREC>() : kNarrowWaves) void
 // One workgroup per part of an i-block (reduce_parts; grid-strided over the
 // work->nib i-blocks of the batch when they outnumber the grid, ib_cl giving
 // each one's cluster): the float64 sum of the rows' split partials
-// (split_sum, G lanes per i-particle as the splits and the workgroup allow)
-// and their results (finish_out).  A launch of its own: the kernel boundary
+// (split_sum) and their results (finish_out).  A launch of its own: the kernel boundary
 // makes every item's partials visible, where a release fence per item would
 // write back the XCD's whole L2 (buffer_wbl2) and an acquire invalidate it,
 // once per item.
 __global__ __launch_bounds__(kWG) void batch_reduce_kernel(BatchArgs b) {
+  __shared__ SplitShared sh;
   const int nib_total = b.work->nib;
   const int P = reduce_parts(nib_total, static_cast<int>(gridDim.x), 64);
   int fl = 0;
   for (int u = blockIdx.x; u < nib_total * P; u += gridDim.x)
-    fl |= reduce_iblock(b, u / P, u % P, P, [](int, const double *) {});
+    fl |= reduce_iblock(b, u / P, u % P, P, sh, [](int, bool) {}, [](int, bool, double2) {});
   if (fl) atomicOr(b.status + kStatusFlags, fl);
 }
 
@@ -412,7 +400,7 @@ hipError_t launch_batch_force(int prec, const BatchArgs &b, int grid, hipStream_
   if (grid <= 0) return hipSuccess;
   const hipError_t e = launch_batch_items(prec, b, grid, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(batch_reduce_kernel, dim3(reduce_grid(grid)), dim3(kWG), 0, s, b);
+  hipLaunchKernelGGL(batch_reduce_kernel, dim3(reduce_grid(grid, b.ni_total)), dim3(kWG), 0, s, b);
   return hipGetLastError();
 }
 

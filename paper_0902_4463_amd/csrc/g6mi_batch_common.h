@@ -105,17 +105,20 @@ __host__ __device__ __forceinline__ int reduce_parts(int nib, int grid, int cap)
   return P;
 }
 
-// The float64 sum of the split partials (split_sum, G lanes per i-particle
-// as the splits and the workgroup allow, laid out by split_lane_map) of part
-// `part` of `nparts` of i-block ibg, and its rows' results (finish_out).
-// The part holds ipw / P consecutive rows, P = min(nparts, ipw) (both powers
-// of two); parts from P on are empty.  Every thread of the workgroup calls
-// it with the same arguments; epi(row, sum) runs on the lane that wrote row
-// `row`, after the write, with the row's sums (acc xyz, jerk xyz, sum m/r).
+// The float64 sum of the split partials (split_sum) of part `part` of
+// `nparts` of i-block ibg, and its rows' results (finish_out).  The part
+// holds ipw / P consecutive rows, P = min(nparts, ipw) (both powers of two);
+// parts from P on are empty.  Every thread of the workgroup calls it with the
+// same arguments.  epi(row, valid, v) runs on every lane of the waves that
+// hold results, after the write: lane c of a row's team of four has
+// components 2c and 2c + 1 in v (acc xyz, jerk xyz, sum m/r).  pre(row,
+// valid) runs on the same lanes before the sum, so that loads epi will need
+// are in flight meanwhile.
 // ONE: the batch is one cluster (cluster 0), whose i-block table need not be
 // read.  Returns the status flags of this thread's rows.
-template <bool ONE = false, class Epi>
-__device__ __forceinline__ int reduce_iblock(const BatchArgs &b, int ibg, int part, int nparts, Epi &&epi) {
+template <bool ONE = false, class Pre, class Epi>
+__device__ __forceinline__ int reduce_iblock(const BatchArgs &b, int ibg, int part, int nparts, SplitShared &sh,
+                                             Pre &&pre, Epi &&epi) {
   const int tid = threadIdx.x;
   const int c = ONE ? 0 : __builtin_amdgcn_readfirstlane(b.ib_cl[ibg]);
   const g6mi_cluster d = b.cl[c];
@@ -124,25 +127,27 @@ __device__ __forceinline__ int reduce_iblock(const BatchArgs &b, int ibg, int pa
   const int P = min(nparts, p.ipw);
   if (part >= P) return 0;
   const int rows = p.ipw / P;
-  const int G = min(split_lanes(p.nsplit, 1), max(1, kWG / rows));
-  int ioff, g, xs;
-  split_lane_map(tid & 63, G, ioff, g, xs);
+  // the whole part at once where it fits (up to 64 rows): fewer rows at a
+  // time, with more lanes each, cost a barrier per round (the reduction of
+  // 256 clusters took 16.8 us so, 13.4 us this way)
+  const int l = 31 - __builtin_clz(min(rows, 64));
+  const int r0 = ib * p.ipw + part * rows; // first row of the part in the cluster
+  const int r1 = min(r0 + rows, d.ni);
   int fl = 0;
-  for (int k0 = 0; k0 < rows; k0 += kWG / G) {
-    const int kk = k0 + (tid >> 6) * xs + ioff;
-    const int il = ib * p.ipw + part * rows + kk;
-    if (kk < rows && il < d.ni) {
-      const size_t e = static_cast<size_t>(p.pbase) + il;
-      double sum[7], best;
-      int bslot;
-      split_sum(p.nsplit, G, g, xs, b.part + e, static_cast<size_t>(d.ni), b.pcap, b.nn_r2 + e, b.nn_slot + e,
-                static_cast<size_t>(d.ni), sum, best, bslot);
-      if (g == 0) {
-        fl |= finish_out(sum, best, bslot, d.ioff + il, b.jm.index, b.fa.nb_count, b.fa.nb_slot, b.nbl != 0, b.acc,
-                         b.jerk, b.pot, b.nnb, b.r2nn, b.status, b.ovf_list, b.ovf_tag, c);
-        epi(d.ioff + il, static_cast<const double *>(sum));
-      }
+  for (int k0 = r0; k0 < r1; k0 += 1 << l) {
+    const int il = k0 + (tid >> 2);
+    const bool valid = tid < (4 << l) && il < r1;
+    pre(d.ioff + il, valid);
+    double2 v;
+    int bslot;
+    split_sum(p.nsplit, l, r1 - k0, b.part, b.nn_slot, static_cast<size_t>(p.pbase) + k0, static_cast<size_t>(d.ni),
+              sh, v, bslot);
+    if ((tid & ~63) < (4 << l)) {
+      fl |= finish_out(v, bslot, valid, d.ioff + il, b.jm.index, b.fa.nb_count, b.fa.nb_slot, b.nbl != 0, b.acc,
+                       b.jerk, b.pot, b.nnb, b.r2nn, b.status, b.ovf_list, b.ovf_tag, c);
+      epi(d.ioff + il, valid, v);
     }
+    __syncthreads(); // sh is written again by the next rows
   }
   return fl;
 }

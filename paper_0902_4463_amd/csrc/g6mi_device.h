@@ -964,73 +964,165 @@ __device__ __forceinline__ void nn_merge(double r2, int sl, double &best, int &b
   }
 }
 
-// The nsplit j-split partials of one i-particle added by a group of G lanes
-// (G a power of two up to 64) of one wave, every lane of the group active:
-// lane g of the group sits xs lanes after lane g - 1 (split_lane_map puts
-// the G lanes of an i-particle xs = 64 / G apart, so that the lanes with the
-// same g read consecutive i-particles).  Component c of split q is at
-// part[q * sstride + c * cstride]; the candidates at nn_r2[q * nstride],
-// nn_slot[q * nstride].  Lane g adds splits g, g + G, g + 2G, ... in that
-// order in float64, its loads issued kAhead splits ahead of the additions
-// (latency, not bandwidth, bounds a long sum); the G lane sums then meet in
-// a butterfly of xor exchanges.  Each exchange adds two equal pairs of
-// operands in either order, so all lanes of the group end with the same
-// bits, and the order of additions is fixed by nsplit and G alone.  G = 1
-// is the plain sum in split order.
-__device__ __forceinline__ void split_sum(int nsplit, int G, int g, int xs, const double *__restrict__ part,
-                                          size_t sstride, size_t cstride, const double *__restrict__ nn_r2,
-                                          const int *__restrict__ nn_slot, size_t nstride, double s[7],
-                                          double &best, int &bslot) {
-  constexpr int kAhead = 4;
+// A split partial is one row of kPartDoubles doubles, [split][row][8]: acc
+// xyz, jerk xyz, sum m/r and the nearest-neighbour r^2, whole in one 64-byte
+// line (its slot sits beside it in an int array [split][row]).  With the
+// components in arrays of their own, a block of few i-particles touched a
+// line per component and split: the sum of 512 splits of 100 i-particles
+// took 15 us.
+__device__ __forceinline__ void store_part(double *__restrict__ part, int *__restrict__ nn_slot, size_t e,
+                                           const Totals &t, double best, int bslot) {
+  double2 *p = reinterpret_cast<double2 *>(part + e * kPartDoubles);
+  p[0] = make_double2(t.acc[0], t.acc[1]);
+  p[1] = make_double2(t.acc[2], t.jrk[0]);
+  p[2] = make_double2(t.jrk[1], t.jrk[2]);
+  p[3] = make_double2(t.pot, best);
+  nn_slot[e] = bslot;
+}
+
+// i-particles per workgroup of a split sum over `rows` of them, as a power of
+// two I <= 64; Q = 64 / I lanes then share the splits of a row.  More lanes
+// per i-particle while each still has more than eight splits to add (one
+// round of loads) and the i-particles do not fill the device by themselves
+// (`fill` workgroups).
+__host__ __device__ constexpr int split_log2rows(int nsplit, long long rows, long long fill) {
+  int l = 6;
+  while (l > 0 && ((rows + (1 << l) - 1) >> l) < fill && (nsplit > 8 * (64 >> l) || (rows << 1) <= (1 << l))) --l;
+  return l;
+}
+
+// LDS of split_sum.
+struct SplitShared {
+  double2 v[kWG];
+  int sl[kWG];
+};
+
+// The nsplit split partials of I = 1 << log2I consecutive rows added by a
+// workgroup: thread t works on components 2c and 2c + 1, c = t mod 4 (the
+// last pair is sum m/r and the nearest neighbour), of row (t / 4) mod I, and
+// adds splits g, g + Q, ..., g = t / (4 I), Q = 64 / I, in float64 with eight
+// 16-byte loads in flight; a wave reads whole 64-byte rows side by side.
+// The Q parts meet in an xor butterfly inside each wave, then through LDS in
+// wave order, so the order of additions is fixed by nsplit and I.  Row r of
+// split q is entry e0 + q * sstride + r; rows from nrows on are padding.
+// Every thread calls it.  On return thread t < 4 I holds components 2c and
+// 2c + 1 of row t / 4 in v (for c = 3 the nearest neighbour's r^2 in v.y and
+// its slot in bslot).  Ends without a barrier after its last LDS reads.
+__device__ __forceinline__ void split_sum(int nsplit, int log2I, int nrows, const double *__restrict__ part,
+                                          const int *__restrict__ nn_slot, size_t e0, size_t sstride,
+                                          SplitShared &sh, double2 &v, int &bslot) {
+  constexpr int kAhead = 8;
+  const int t = threadIdx.x, c = t & 3, il = (t >> 2) & ((1 << log2I) - 1);
+  const int g = t >> (2 + log2I), Q = 64 >> log2I;
+  const bool nn = c == 3;
+  double s0 = 0.0, s1 = nn ? INFINITY : 0.0;
+  int bs = -1;
+  auto add = [&](double2 x, int sl) {
+    s0 += x.x;
+    if (nn) nn_merge(x.y, sl, s1, bs);
+    else s1 += x.y;
+  };
+  if (il < nrows) {
+    const double2 *src = reinterpret_cast<const double2 *>(part) + (e0 + il) * (kPartDoubles / 2) + c;
+    for (int q0 = g; q0 < nsplit; q0 += kAhead * Q) {
+      double2 x[kAhead];
+      int sl[kAhead];
 #pragma unroll
-  for (int c = 0; c < 7; ++c) s[c] = 0.0;
-  best = INFINITY;
-  bslot = -1;
-  int q = g;
-  for (; q + (kAhead - 1) * G < nsplit; q += kAhead * G) {
-    double v[kAhead][7], r2[kAhead];
-    int sl[kAhead];
+      for (int u = 0; u < kAhead; ++u) {
+        // past the last split: the last one again, not added (loads without
+        // a branch each)
+        const size_t e = static_cast<size_t>(min(q0 + u * Q, nsplit - 1)) * sstride;
+        x[u] = src[e * (kPartDoubles / 2)];
+        sl[u] = nn_slot[e0 + il + e];
+      }
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const size_t k = static_cast<size_t>(q + u * G);
-#pragma unroll
-      for (int c = 0; c < 7; ++c) v[u][c] = part[k * sstride + c * cstride];
-      r2[u] = nn_r2[k * nstride];
-      sl[u] = nn_slot[k * nstride];
-    }
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-#pragma unroll
-      for (int c = 0; c < 7; ++c) s[c] += v[u][c];
-      nn_merge(r2[u], sl[u], best, bslot);
+      for (int u = 0; u < kAhead; ++u)
+        if (q0 + u * Q < nsplit) add(x[u], sl[u]);
     }
   }
-  for (; q < nsplit; q += G) {
-    const size_t k = static_cast<size_t>(q);
-#pragma unroll
-    for (int c = 0; c < 7; ++c) s[c] += part[k * sstride + c * cstride];
-    nn_merge(nn_r2[k * nstride], nn_slot[k * nstride], best, bslot);
+  for (int m = 4 << log2I; m < 64; m <<= 1) {
+    const double2 o = make_double2(__shfl_xor(s0, m), __shfl_xor(s1, m));
+    add(o, __shfl_xor(bs, m));
   }
-  for (int m = 1; m < G; m <<= 1) {
+  const int stride = (4 << log2I) < 64 ? 64 : (4 << log2I); // threads between two parts left
+  if (stride < kWG) {
+    sh.v[t] = make_double2(s0, s1);
+    sh.sl[t] = bs;
+    __syncthreads();
+    if (t < (4 << log2I))
+      for (int p = t + stride; p < kWG; p += stride) add(sh.v[p], sh.sl[p]);
+  }
+  v = make_double2(s0, s1);
+  bslot = bs;
+}
+
+// Ascending particle indices of a neighbour list of cnt <= kNbMax slots at
+// lst, for a whole wave: the four lanes of a row's team sort lists of up to
+// 16 entries side by side (four per lane, ranked by counting the smaller
+// ones), the wave takes longer ones one after the other.  One lane sorting
+// its row by insertion in memory took a dependent load per step.  Every lane
+// of the wave calls it; cnt = 0 for teams without a list.  Equal indices are
+// ranked by position.
+__device__ __forceinline__ void sort_lists(int cnt, int *__restrict__ lst, const int *__restrict__ jindex) {
+  const int lane = threadIdx.x & 63, c = lane & 3, base = lane & ~3;
+  if (!__any(cnt > 0)) return;
+  const int small = cnt <= 16 ? cnt : 0;
+  int key[4], rank[4];
 #pragma unroll
-    for (int c = 0; c < 7; ++c) s[c] += __shfl_xor(s[c], m * xs);
-    const double ob = __shfl_xor(best, m * xs);
-    const int os = __shfl_xor(bslot, m * xs);
-    nn_merge(ob, os, best, bslot);
+  for (int k = 0; k < 4; ++k) {
+    key[k] = c + 4 * k < small ? jindex[lst[c + 4 * k]] : 0x7fffffff;
+    rank[k] = 0;
+  }
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    if (!__any(4 * b < small)) break;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int o = __shfl(key[b], base + q);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) rank[k] += o < key[k] || (o == key[k] && q + 4 * b < c + 4 * k);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (c + 4 * k < small) lst[rank[k]] = key[k];
+  unsigned long long big = __ballot(cnt > 16 && c == 0);
+  while (big) {
+    const int src = __builtin_ctzll(big);
+    big &= big - 1;
+    const int n = __shfl(cnt, src);
+    const unsigned long long a = static_cast<unsigned long long>(reinterpret_cast<uintptr_t>(lst));
+    int *l = reinterpret_cast<int *>(static_cast<uintptr_t>(__shfl(a, src)));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      key[k] = lane + 64 * k < n ? jindex[l[lane + 64 * k]] : 0x7fffffff;
+      rank[k] = 0;
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      for (int q = 0; q < 64 && 64 * b + q < n; ++q) {
+        const int o = __shfl(key[b], q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rank[k] += o < key[k] || (o == key[k] && q + 64 * b < lane + 64 * k);
+      }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (lane + 64 * k < n) l[rank[k]] = key[k];
   }
 }
 
-// Final result of one i-particle from its summed partials s (acc xyz, jerk
-// xyz, sum m/r) and nearest-neighbour candidate: outputs go to row `row`,
-// and its neighbour list is turned from slots into particle indices sorted
-// ascending.  An overflowed list is queued in ovf_list (and its tag in
-// ovf_tag when given) for the exact pass, counted in
-// status[kStatusOverflowCount].  Returns the status flags of the row
-// (bit 0 non-finite output, bit 1 neighbour overflow).
+// Final results of the rows whose sums split_sum left in a wave: lane c of
+// a row's team of four writes its components (v, bslot) to row `row` of the
+// outputs (valid: the team has a row), and the row's neighbour list is turned from slots into
+// particle indices sorted ascending.  An overflowed list is queued in
+// ovf_list (and its tag in ovf_tag when given) for the exact pass, counted in
+// status[kStatusOverflowCount].  Every lane of the wave calls it.  Returns
+// this lane's status flags (bit 0 non-finite output, bit 1 neighbour
+// overflow).
 // nb_work: the interaction kernel counted the row's neighbours there instead
 // of in nb_count; the count is moved to nb_count and nb_work[row] cleared
 // for the next calculation (so that no launch has to clear it first).
-__device__ __forceinline__ int finish_out(const double s[7], double best, int bslot, int row,
+__device__ __forceinline__ int finish_out(double2 v, int bslot, bool valid, int row,
                                           const int *__restrict__ jindex,
                                           int *__restrict__ nb_count, int *__restrict__ nb_slot,
                                           bool nbl, double *__restrict__ acc, double *__restrict__ jerk,
@@ -1038,69 +1130,43 @@ __device__ __forceinline__ int finish_out(const double s[7], double best, int bs
                                           double *__restrict__ r2nn, int *__restrict__ status,
                                           int *__restrict__ ovf_list, int *__restrict__ ovf_tag, int tag,
                                           int *__restrict__ nb_work = nullptr) {
-  const size_t i = static_cast<size_t>(row);
-  bool finite = true;
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    acc[3 * i + d] = s[d];
-    jerk[3 * i + d] = s[3 + d];
-    finite = finite && isfinite(s[d]) && isfinite(s[3 + d]);
-  }
-  pot[i] = -s[6];
-  finite = finite && isfinite(s[6]);
-  if (nnb) nnb[i] = bslot >= 0 ? jindex[bslot] : -1;
-  if (r2nn) r2nn[i] = bslot >= 0 ? best : INFINITY;
-  int fl = finite ? 0 : 1;
-  if (!nbl && nb_work) nb_count[i] = 0; // no list: no count left from an earlier call
-  if (nbl) {
-    int cnt;
-    if (nb_work) {
-      cnt = nb_work[i];
-      nb_work[i] = 0;
-      nb_count[i] = cnt;
+  const int c = threadIdx.x & 3;
+  const size_t i = static_cast<size_t>(valid ? row : 0);
+  int fl = 0, cnt = 0;
+  if (valid) {
+    if (nbl) cnt = nb_work ? nb_work[i] : nb_count[i];
+    if (c == 0) {
+      acc[3 * i] = v.x;
+      acc[3 * i + 1] = v.y;
+    } else if (c == 1) {
+      acc[3 * i + 2] = v.x;
+      jerk[3 * i] = v.y;
+    } else if (c == 2) {
+      jerk[3 * i + 1] = v.x;
+      jerk[3 * i + 2] = v.y;
     } else {
-      cnt = nb_count[i];
+      pot[i] = -v.x;
+      if (nnb) nnb[i] = bslot >= 0 ? jindex[bslot] : -1;
+      if (r2nn) r2nn[i] = bslot >= 0 ? v.y : INFINITY;
     }
-    int *lst = nb_slot + i * kNbMax;
+    if (!isfinite(v.x) || (c < 3 && !isfinite(v.y))) fl = 1;
+  }
+  // every lane of the team has read the counter before it is cleared
+  __builtin_amdgcn_wave_barrier();
+  if (valid && c == 0) {
+    if (nb_work) {
+      nb_count[i] = cnt; // zero without lists: no count left from an earlier call
+      if (nbl) nb_work[i] = 0;
+    }
     if (cnt > kNbMax) { // kept set decided later by the exact pass
       fl |= 2;
       const int q = atomicAdd(status + kStatusOverflowCount, 1);
       ovf_list[q] = row;
       if (ovf_tag) ovf_tag[q] = tag;
-      return fl;
-    }
-    for (int a = 0; a < cnt; ++a) lst[a] = jindex[lst[a]];
-    for (int a = 1; a < cnt; ++a) { // insertion sort: lists are short
-      const int key = lst[a];
-      int b = a - 1;
-      while (b >= 0 && lst[b] > key) {
-        lst[b + 1] = lst[b];
-        --b;
-      }
-      lst[b + 1] = key;
     }
   }
+  if (nbl) sort_lists(cnt <= kNbMax ? cnt : 0, nb_slot + i * kNbMax, jindex);
   return fl;
-}
-
-// Lanes per i-particle of a split sum: one for up to 8 splits, else about a
-// quarter of the splits, at most a wave, and fewer where the i-particles
-// alone give lanes enough (ni * G at most 2^17).
-__host__ __device__ constexpr int split_lanes(int nsplit, long long ni) {
-  int G = 1;
-  if (nsplit > 8)
-    while (G < 64 && 4 * (2 * G) <= nsplit && ni * (2 * G) <= (1LL << 17)) G <<= 1;
-  return G;
-}
-
-// Lane l of a wave, in groups of G lanes per i-particle (G a power of two up
-// to 64): the wave holds w = 64 / G consecutive i-particles, lane l serving
-// i-particle l mod w as member g = l / w of its group; the members of a
-// group sit w lanes apart.
-__device__ __forceinline__ void split_lane_map(int lane, int G, int &ioff, int &g, int &xs) {
-  xs = 64 / G;
-  ioff = lane & (xs - 1);
-  g = lane / xs;
 }
 
 // ---------------------------------------------- neighbour-list overflow

@@ -178,66 +178,81 @@ __device__ __forceinline__ double quantise(double dt, double dt_min, double dt_m
   return ldexp(1.0, e - 1);
 }
 
-// Corrector (Makino & Aarseth 1992) for block position q at block time tb,
-// given its new force sums f (acc xyz, jerk xyz, sum m/r, as the batch
-// reduction wrote them to acc1, jrk1 and pot1 = -f[6]), then the Aarseth
-// criterion with the second derivative at the end of the step, and the
-// block rule: halve while too long, double only when the time is a multiple
-// of the doubled step.  Returns the new step.
-__device__ __forceinline__ double correct_particle(const HermiteArgs &h, int q, double tb, const double *f) {
+// What the corrector needs of the particle at block position q besides its
+// new force: loaded before the split sums, by the four lanes of its team (lane
+// c takes component c of the vectors; the last lane repeats component 2).
+struct CorrectState {
+  int k = 0;
+  double t = 0, dt = 0, a0 = 0, j0 = 0, xp = 0, vp = 0;
+  __device__ __forceinline__ void load(const HermiteArgs &h, int q, int c) {
+    k = h.active[q];
+    const size_t e = static_cast<size_t>(c) * h.jm.cap + k, r = 3 * static_cast<size_t>(q) + c;
+    xp = h.xi[r];
+    vp = h.vi[r];
+    t = h.jm.t[k];
+    dt = h.dt[k];
+    a0 = h.acc[e];
+    j0 = h.jrk[e];
+  }
+};
+
+// Corrector (Makino & Aarseth 1992) of a particle (s) at block time tb, given
+// its new force sums f (acc xyz, jerk xyz, sum m/r), then the Aarseth
+// criterion with the second derivative at the end of the step, and the block
+// rule: halve while too long, double only when the time is a multiple of the
+// doubled step.  The team's four lanes call it: lane c corrects component c,
+// the norms collect the components by lane exchange, and all lanes return the
+// new step.
+__device__ __forceinline__ double correct_particle(const HermiteArgs &h, const CorrectState &s, int c, double tb,
+                                                   const double *f) {
 #pragma clang fp contract(off)
   HermiteCtl *ctl = h.ctl;
-  const int k = h.active[q];
   const size_t cap = h.jm.cap;
-  const double dt = tb - h.jm.t[k];
-  double a0[3], j0[3], a1[3], j1[3], a2[3], a3[3], a2e[3];
+  const double dt = tb - s.t;
+  const int d = min(c, 2);
+  const double a1[3] = {f[0], f[1], f[2]}, j1[3] = {f[3], f[4], f[5]};
   bool finite = true;
-  for (int d = 0; d < 3; ++d) {
-    a0[d] = h.acc[d * cap + k];
-    j0[d] = h.jrk[d * cap + k];
-    a1[d] = f[d];
-    j1[d] = f[3 + d];
-    finite = finite && isfinite(a1[d]) && isfinite(j1[d]);
-  }
+  for (int u = 0; u < 3; ++u) finite = finite && isfinite(a1[u]) && isfinite(j1[u]);
+  const double a1d = d == 0 ? a1[0] : (d == 1 ? a1[1] : a1[2]);
+  const double j1d = d == 0 ? j1[0] : (d == 1 ? j1[1] : j1[2]);
   const double dt2 = dt * dt, dt3 = dt2 * dt, dt4 = dt3 * dt, dt5 = dt4 * dt;
-  for (int d = 0; d < 3; ++d) {
-    a2[d] = (-6.0 * (a0[d] - a1[d]) - dt * (4.0 * j0[d] + 2.0 * j1[d])) / dt2;
-    a3[d] = (12.0 * (a0[d] - a1[d]) + 6.0 * dt * (j0[d] + j1[d])) / dt3;
-  }
-  double xp[3], vp[3];
-  for (int d = 0; d < 3; ++d) {
-    xp[d] = h.xi[3 * static_cast<size_t>(q) + d];
-    vp[d] = h.vi[3 * static_cast<size_t>(q) + d];
-  }
-  for (int d = 0; d < 3; ++d) {
-    const double x1 = xp[d] + a2[d] * dt4 / 24.0 + a3[d] * dt5 / 120.0;
-    const double v1 = vp[d] + a2[d] * dt3 / 6.0 + a3[d] * dt4 / 24.0;
-    a2e[d] = a2[d] + dt * a3[d];
-    h.jm.x[d * cap + k] = x1;
-    h.jm.v[d * cap + k] = v1;
-    h.acc[d * cap + k] = a1[d];
-    h.jrk[d * cap + k] = j1[d];
-    h.jm.a2[d * cap + k] = a1[d] / 2.0;
-    h.jm.j6[d * cap + k] = j1[d] / 6.0;
+  const double a2d = (-6.0 * (s.a0 - a1d) - dt * (4.0 * s.j0 + 2.0 * j1d)) / dt2;
+  const double a3d = (12.0 * (s.a0 - a1d) + 6.0 * dt * (s.j0 + j1d)) / dt3;
+  const double a2ed = a2d + dt * a3d;
+  const int base = threadIdx.x & 60;
+  double a3[3], a2e[3];
+  for (int u = 0; u < 3; ++u) {
+    a3[u] = __shfl(a3d, base + u);
+    a2e[u] = __shfl(a2ed, base + u);
   }
   const double na1 = norm3(a1), nj1 = norm3(j1), na3 = norm3(a3), na2e = norm3(a2e);
   const double num = na1 * na2e + nj1 * nj1;
   const double den = nj1 * na3 + na2e * na2e;
   const double dt_new = sqrt(h.eta * num / fmax(den, 1e-300));
-  const double old = h.dt[k];
+  const double old = s.dt;
   double nw = old;
   while (dt_new < nw && nw > h.dt_min) nw *= 0.5; // never below dt_min
   if (dt_new >= 2.0 * old && fmod(tb, 2.0 * old) == 0.0 && 2.0 * old <= h.dt_max) nw = 2.0 * old;
-  h.jm.t[k] = tb;
-  h.dt[k] = nw;
-  h.pot[k] = -f[6];
-  if (!finite) atomicOr(&ctl->flags, 1);
+  if (c < 3) {
+    const size_t e = static_cast<size_t>(c) * cap + s.k;
+    h.jm.x[e] = s.xp + a2d * dt4 / 24.0 + a3d * dt5 / 120.0;
+    h.jm.v[e] = s.vp + a2d * dt3 / 6.0 + a3d * dt4 / 24.0;
+    h.acc[e] = a1d;
+    h.jrk[e] = j1d;
+    h.jm.a2[e] = a1d / 2.0;
+    h.jm.j6[e] = j1d / 6.0;
+  } else {
+    h.jm.t[s.k] = tb;
+    h.dt[s.k] = nw;
+    h.pot[s.k] = -f[6];
+    if (!finite) atomicOr(&ctl->flags, 1);
+  }
   return nw;
 }
 
 // The block's forces finished from the split partials (reduce_iblock, one
 // workgroup per part of an i-block, at most kHsReduceWgs workgroups with
-// rows) and each particle corrected by the lane that finished it
+// rows) and each particle corrected by the lanes that finished it
 // (correct_particle); the minimum of their new t + dt is folded into the
 // next block time, one atomic per workgroup with rows.
 __global__ __launch_bounds__(256) void hs_correct_kernel(HermiteArgs h, BatchArgs b) {
@@ -251,13 +266,27 @@ __global__ __launch_bounds__(256) void hs_correct_kernel(HermiteArgs h, BatchArg
   }
   unsigned long long next = kKeyInf;
   int fl = 0;
+  __shared__ SplitShared sh;
+  const int c = threadIdx.x & 3;
+  CorrectState st;
   const int nib_total = b.work->nib;
   const int P = reduce_parts(nib_total, min(static_cast<int>(gridDim.x), kHsReduceWgs), 64);
   for (int u = blockIdx.x; u < nib_total * P; u += gridDim.x)
-    fl |= reduce_iblock<true>(b, u / P, u % P, P, [&](int q, const double *sum) {
-      const unsigned long long key = order_key(tb + correct_particle(h, q, tb, sum));
-      next = key < next ? key : next;
-    });
+    fl |= reduce_iblock<true>(
+        b, u / P, u % P, P, sh,
+        [&](int q, bool valid) {
+          if (valid) st.load(h, q, min(c, 2));
+        },
+        [&](int q, bool valid, double2 v) {
+          const int base = threadIdx.x & 60;
+          const double sum[7] = {__shfl(v.x, base),     __shfl(v.y, base),     __shfl(v.x, base + 1),
+                                 __shfl(v.y, base + 1), __shfl(v.x, base + 2), __shfl(v.y, base + 2),
+                                 __shfl(v.x, base + 3)};
+          if (valid) {
+            const unsigned long long key = order_key(tb + correct_particle(h, st, c, tb, sum));
+            next = key < next ? key : next;
+          }
+        });
   if (fl) atomicOr(b.status + kStatusFlags, fl);
   // the next block time, second part: this block's particles
   key_min(next, &ctl->key[ctl->phase]);
@@ -340,7 +369,7 @@ hipError_t launch_hs_start(const HermiteArgs &h, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_hs_correct(const HermiteArgs &h, const BatchArgs &b, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(hs_correct_kernel, dim3(static_cast<unsigned>(reduce_grid(grid > 0 ? grid : 1))), dim3(256), 0, s, h, b);
+  hipLaunchKernelGGL(hs_correct_kernel, dim3(static_cast<unsigned>(grid > 0 ? grid : 1)), dim3(256), 0, s, h, b);
   return hipGetLastError();
 }
 

@@ -47,13 +47,7 @@ constexpr int kWG = 256;          // lanes per workgroup: four wave64
 constexpr int kTile = G6MI_TILE;  // j-records staged in LDS per tile
 constexpr int kNbMax = 256;       // neighbour slots per i-particle
 constexpr int kFusedDepth = G6MI_FUSED_DEPTH;
-// Reduction of blocks of at most kFewMaxNi i-particles over more than 64
-// splits: one workgroup per i-particle, at most kFewSplitsPerLane splits per lane.
-#ifndef G6MI_FEW_MAX_NI
-#define G6MI_FEW_MAX_NI 256
-#endif
-constexpr int kFewMaxNi = G6MI_FEW_MAX_NI;
-constexpr int kFewSplitsPerLane = 4;
+constexpr int kPartDoubles = 8;   // doubles per row of a split partial (see store_part)
 
 // Status words of one calculation in device memory (zeroed by the predictor
 // launch): flags (bit 0 non-finite output, bit 1 neighbour overflow) and the
@@ -89,9 +83,8 @@ struct ForceArgs {
   double eps2 = 0.0;
   int ipw = kWG;               // i-particles per workgroup, power of two
   int log2ipw = 8;
-  // outputs of the j-split s in [0, nsplit), component-major:
-  double *part = nullptr;      // [nsplit][7][ni]: acc xyz, jerk xyz, sum m/r
-  double *nn_r2 = nullptr;     // [nsplit][ni]
+  // outputs of the j-split s in [0, nsplit):
+  double *part = nullptr;      // [nsplit][ni][kPartDoubles]: acc xyz, jerk xyz, sum m/r, neighbour r^2
   int *nn_slot = nullptr;      // [nsplit][ni]
   int *nb_count = nullptr;     // [ni]   (zeroed by the predictor launch; see force_fused)
   int *nb_slot = nullptr;      // [ni][kNbMax]
@@ -124,8 +117,7 @@ hipError_t launch_zero(int n, int *p, hipStream_t s);
 // or null where partials sit at their own rows.  nb_work: the counters of a
 // force_fused launch (moved to nb_count and cleared), or null.
 hipError_t launch_reduce(int nsplit, int ni, const int *iperm, const double *part,
-                         const double *nn_r2, const int *nn_slot,
-                         const int *jindex, int *nb_count, int *nb_slot,
+                         const int *nn_slot, const int *jindex, int *nb_count, int *nb_slot,
                          bool nbl, double *acc, double *jerk, double *pot,
                          int *nnb, double *r2nn, int *status, int *ovf_list,
                          hipStream_t s, int *nb_work = nullptr);
@@ -225,15 +217,19 @@ struct BatchPlan {
   long long pbase;
 };
 
-// Workgroups of a batch reduction (batch_reduce_kernel, hs_correct_kernel)
-// for a persistent grid of `grid`: kReduceGridMul times as many, so that
-// the i-blocks of a small batch are cut into parts (reduce_parts) and
-// their split sums run with more loads in flight.
+// Workgroups of batch_reduce_kernel for a persistent grid of `grid` and
+// `rows` i-rows: kReduceGridMul times as many, so that the i-blocks of a
+// small batch are cut into parts (reduce_parts) and their split sums run with
+// more loads in flight, but no more than one per four rows (the launch of
+// 3072 workgroups takes 3 us by itself).
 #ifndef G6MI_REDUCE_GRID_MUL
 #define G6MI_REDUCE_GRID_MUL 4
 #endif
 constexpr int kReduceGridMul = G6MI_REDUCE_GRID_MUL;
-__host__ __device__ constexpr int reduce_grid(int grid) { return grid * kReduceGridMul; }
+__host__ __device__ constexpr int reduce_grid(int grid, int rows) {
+  const int most = grid * kReduceGridMul, need = (rows + 3) / 4;
+  return need < 1 ? 1 : (need < most ? need : most);
+}
 
 // Most workgroups with rows in hs_correct_kernel: each ends with one atomic
 // on the next block time, and a burst of them on one address queues up.
@@ -262,10 +258,8 @@ struct BatchArgs {
   BatchTune tune;
   JMem jm;
   ForceArgs fa;            // i-arrays over rows 0..ni_total-1; nb_count, nb_slot
-  double *part = nullptr;  // [7][pcap] split partials
-  double *nn_r2 = nullptr; // [pcap]
+  double *part = nullptr;  // [pcap][kPartDoubles] split partials
   int *nn_slot = nullptr;  // [pcap]
-  size_t pcap = 0;
   int *ib_cl = nullptr;    // [ni_total] cluster of each i-block (at most one per row)
   int nbl = 1;
   double *acc = nullptr, *jerk = nullptr, *pot = nullptr, *r2nn = nullptr;

@@ -93,20 +93,9 @@ __global__ __launch_bounds__(kWG, wide_waves<PREC>()) void force_wide(ForceArgs 
   // re-read from global memory (every slot is < nj)
   w.resolve(jp, 0);
 
-  const size_t ni = static_cast<size_t>(a.ni);
-  auto store = [&](int i, const Totals &t, real_t<PREC> best, int bslot) {
-    double *p = a.part + static_cast<size_t>(blockIdx.y) * 7 * ni + i;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      p[d * ni] = t.acc[d];
-      p[(3 + d) * ni] = t.jrk[d];
-    }
-    p[6 * ni] = t.pot;
-    a.nn_r2[blockIdx.y * ni + i] = static_cast<double>(best);
-    a.nn_slot[blockIdx.y * ni + i] = bslot;
-  };
-  if (w.v0) store(i0, w.t0, w.ebest0, w.eslot0);
-  if (w.v1) store(i1, w.t1, w.ebest1, w.eslot1);
+  const size_t e0 = static_cast<size_t>(blockIdx.y) * a.ni;
+  if (w.v0) store_part(a.part, a.nn_slot, e0 + i0, w.t0, static_cast<double>(w.ebest0), w.eslot0);
+  if (w.v1) store_part(a.part, a.nn_slot, e0 + i1, w.t1, static_cast<double>(w.ebest1), w.eslot1);
 }
 
 // K float4 per lane of a tile of n4 float4 (lane tid holds elements tid,
@@ -189,18 +178,8 @@ __global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a) {
   double bestd;
   int bslot;
   n.lane_sum(reinterpret_cast<double *>(lds), tid, il, ipw, bestd, bslot);
-  if (n.sub == 0 && n.valid) {
-    const size_t ni = static_cast<size_t>(a.ni);
-    double *p = a.part + static_cast<size_t>(blockIdx.y) * 7 * ni + i;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      p[d * ni] = n.t.acc[d];
-      p[(3 + d) * ni] = n.t.jrk[d];
-    }
-    p[6 * ni] = n.t.pot;
-    a.nn_r2[blockIdx.y * ni + i] = bestd;
-    a.nn_slot[blockIdx.y * ni + i] = bslot;
-  }
+  if (n.sub == 0 && n.valid)
+    store_part(a.part, a.nn_slot, static_cast<size_t>(blockIdx.y) * a.ni + i, n.t, bestd, bslot);
 }
 
 // ------------------------------------ small blocks, predictor fused in
@@ -254,18 +233,8 @@ __global__ __launch_bounds__(kWG) void force_fused(ForceArgs a, JMem jm, double 
   double bestd;
   int bslot;
   n.lane_sum(reinterpret_cast<double *>(lds), tid, il, ipw, bestd, bslot);
-  if (n.sub == 0 && n.valid) {
-    const size_t ni = static_cast<size_t>(a.ni);
-    double *p = a.part + static_cast<size_t>(blockIdx.y) * 7 * ni + i;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      p[d * ni] = n.t.acc[d];
-      p[(3 + d) * ni] = n.t.jrk[d];
-    }
-    p[6 * ni] = n.t.pot;
-    a.nn_r2[blockIdx.y * ni + i] = bestd;
-    a.nn_slot[blockIdx.y * ni + i] = bslot;
-  }
+  if (n.sub == 0 && n.valid)
+    store_part(a.part, a.nn_slot, static_cast<size_t>(blockIdx.y) * a.ni + i, n.t, bestd, bslot);
 }
 
 // One i-particle (ipw = 1, all 256 lanes on it): lane tid takes records
@@ -319,18 +288,7 @@ __global__ __launch_bounds__(kWG) void force_fused_one(ForceArgs a, JMem jm, dou
   double bestd;
   int bslot;
   n.lane_sum(red, tid, 0, 1, bestd, bslot);
-  if (tid == 0) {
-    const size_t ni = static_cast<size_t>(a.ni);
-    double *p = a.part + static_cast<size_t>(blockIdx.y) * 7 * ni;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      p[d * ni] = n.t.acc[d];
-      p[(3 + d) * ni] = n.t.jrk[d];
-    }
-    p[6 * ni] = n.t.pot;
-    a.nn_r2[blockIdx.y * ni] = bestd;
-    a.nn_slot[blockIdx.y * ni] = bslot;
-  }
+  if (tid == 0) store_part(a.part, a.nn_slot, static_cast<size_t>(blockIdx.y) * a.ni, n.t, bestd, bslot);
 }
 
 // Clear n counters (a new or regrown nb_work buffer).
@@ -341,104 +299,34 @@ __global__ __launch_bounds__(256) void zero_kernel(int n, int *__restrict__ p) {
 
 // --------------------------------------------------------------- reduction
 
-// 2^log2G lanes per i-particle (split_sum, then finish_out on the first
-// lane), laid out by split_lane_map: float64 sum over the j-splits in a fixed
-// order, nearest-neighbour minimum, neighbour-list finalisation.  The
-// partials of position i belong to row iperm[i] when iperm is given (the
-// spatially ordered kernel writes them in sorted order), else to row i.
+// 2^log2I i-particles per workgroup (split_sum, then finish_out): the float64
+// sum over the j-splits in a fixed order, nearest-neighbour minimum,
+// neighbour-list finalisation.  Bound by the latency of its loads for small
+// blocks and by HBM for large ones: against one or 64 lanes per i-particle
+// over component arrays, 512 splits of 100 i-particles take 7.1 us (15.3),
+// of 3000 27 us (51), 8 splits of 2^20 226 us (260).  The partials of
+// position i belong to row iperm[i] when iperm is given (the spatially
+// ordered kernel writes them in sorted order), else to row i.
 // status[kStatusFlags] bit 0: a non-finite output; bit 1: a neighbour list
 // overflowed (those i-particles are queued in ovf_list for nb_exact_kernel).
 __global__ __launch_bounds__(256) void reduce_kernel(
-    int nsplit, int ni, int log2G, const int *__restrict__ iperm, const double *__restrict__ part,
-    const double *__restrict__ nn_r2, const int *__restrict__ nn_slot,
-    const int *__restrict__ jindex, int *__restrict__ nb_count,
+    int nsplit, int ni, int log2I, const int *__restrict__ iperm, const double *__restrict__ part,
+    const int *__restrict__ nn_slot, const int *__restrict__ jindex, int *__restrict__ nb_count,
     int *__restrict__ nb_slot, int nbl, double *__restrict__ acc,
     double *__restrict__ jerk, double *__restrict__ pot, int *__restrict__ nnb,
     double *__restrict__ r2nn, int *__restrict__ status, int *__restrict__ ovf_list,
     int *__restrict__ nb_work) {
-  const long long t = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;
-  const int G = 1 << log2G;
-  int ioff, g, xs;
-  split_lane_map(static_cast<int>(t & 63), G, ioff, g, xs);
-  const long long i = (t >> 6) * xs + ioff;
-  if (i >= ni) return; // whole groups: the G lanes of an i-particle share i
-  const size_t n = static_cast<size_t>(ni);
-  double sum[7], best;
+  __shared__ SplitShared sh;
+  const int tid = threadIdx.x;
+  const int i0 = static_cast<int>(blockIdx.x) << log2I;
+  double2 v;
   int bslot;
-  split_sum(nsplit, G, g, xs, part + i, 7 * n, n, nn_r2 + i, nn_slot + i, n, sum, best, bslot);
-  if (g != 0) return;
-  const int row = iperm ? iperm[i] : static_cast<int>(i);
-  const int fl = finish_out(sum, best, bslot, row, jindex, nb_count, nb_slot, nbl != 0, acc, jerk, pot, nnb, r2nn,
-                            status, ovf_list, nullptr, 0, nb_work);
-  if (fl) atomicOr(status + kStatusFlags, fl);
-}
-
-// A block of few i-particles over many j-splits: one workgroup per
-// i-particle.  Lane g adds splits g, g + 256, ... in float64 (all of its
-// loads issued before the additions), the 64 lane sums of a wave meet in an
-// xor butterfly, and lane 0 adds the four wave sums in wave order: the order
-// of additions is fixed by nsplit alone.  The 64 lanes per particle of
-// reduce_kernel need two or more rounds of dependent loads for 512 splits
-// and occupy a handful of workgroups; here each lane's loads are one round.
-__global__ __launch_bounds__(256) void reduce_few_kernel(
-    int nsplit, int ni, const int *__restrict__ iperm, const double *__restrict__ part,
-    const double *__restrict__ nn_r2, const int *__restrict__ nn_slot,
-    const int *__restrict__ jindex, int *__restrict__ nb_count,
-    int *__restrict__ nb_slot, int nbl, double *__restrict__ acc,
-    double *__restrict__ jerk, double *__restrict__ pot, int *__restrict__ nnb,
-    double *__restrict__ r2nn, int *__restrict__ status, int *__restrict__ ovf_list,
-    int *__restrict__ nb_work) {
-  constexpr int kPer = kFewSplitsPerLane;
-  const int i = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const size_t n = static_cast<size_t>(ni);
-  double v[kPer][7], r2[kPer];
-  int sl[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int q = tid + u * 256;
-    const bool ok = q < nsplit;
-    const size_t k = static_cast<size_t>(ok ? q : 0);
-#pragma unroll
-    for (int c = 0; c < 7; ++c) v[u][c] = ok ? part[k * 7 * n + c * n + i] : 0.0;
-    r2[u] = ok ? nn_r2[k * n + i] : INFINITY;
-    sl[u] = ok ? nn_slot[k * n + i] : -1;
-  }
-  double s[7], best = INFINITY;
-  int bslot = -1;
-#pragma unroll
-  for (int c = 0; c < 7; ++c) s[c] = 0.0;
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-#pragma unroll
-    for (int c = 0; c < 7; ++c) s[c] += v[u][c];
-    nn_merge(r2[u], sl[u], best, bslot);
-  }
-  for (int m = 1; m < 64; m <<= 1) {
-#pragma unroll
-    for (int c = 0; c < 7; ++c) s[c] += __shfl_xor(s[c], m);
-    const double ob = __shfl_xor(best, m);
-    const int os = __shfl_xor(bslot, m);
-    nn_merge(ob, os, best, bslot);
-  }
-  __shared__ double s_red[4][8];
-  __shared__ int s_slot[4];
-  if (lane == 0) {
-#pragma unroll
-    for (int c = 0; c < 7; ++c) s_red[wave][c] = s[c];
-    s_red[wave][7] = best;
-    s_slot[wave] = bslot;
-  }
-  __syncthreads();
-  if (tid != 0) return;
-#pragma unroll
-  for (int w = 1; w < 4; ++w) {
-#pragma unroll
-    for (int c = 0; c < 7; ++c) s[c] += s_red[w][c];
-    nn_merge(s_red[w][7], s_slot[w], best, bslot);
-  }
-  const int row = iperm ? iperm[i] : i;
-  const int fl = finish_out(s, best, bslot, row, jindex, nb_count, nb_slot, nbl != 0, acc, jerk, pot, nnb, r2nn,
+  split_sum(nsplit, log2I, ni - i0, part, nn_slot, static_cast<size_t>(i0), static_cast<size_t>(ni), sh, v, bslot);
+  if ((tid & ~63) >= (4 << log2I)) return; // whole waves without a row
+  const int i = i0 + (tid >> 2);
+  const bool valid = tid < (4 << log2I) && i < ni;
+  const int row = valid ? (iperm ? iperm[i] : i) : 0;
+  const int fl = finish_out(v, bslot, valid, row, jindex, nb_count, nb_slot, nbl != 0, acc, jerk, pot, nnb, r2nn,
                             status, ovf_list, nullptr, 0, nb_work);
   if (fl) atomicOr(status + kStatusFlags, fl);
 }
@@ -569,6 +457,10 @@ hipError_t scratch_region(int device, void **ptr, size_t *bytes) {
 
 // ---------------------------------------------------------------- launchers
 
+// Workgroups of the reduction from which on more lanes per i-particle gain
+// nothing (about four per compute unit).
+constexpr int kReduceFill = 1024;
+
 static inline unsigned blocks_for(long n) { return static_cast<unsigned>((n + 255) / 256); }
 
 hipError_t launch_predict(int prec, int nj, double ti, const JMem &jm, void *out,
@@ -651,25 +543,15 @@ hipError_t launch_zero(int n, int *p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(int nsplit, int ni, const int *iperm, const double *part, const double *nn_r2,
+hipError_t launch_reduce(int nsplit, int ni, const int *iperm, const double *part,
                          const int *nn_slot, const int *jindex, int *nb_count, int *nb_slot,
                          bool nbl, double *acc, double *jerk, double *pot, int *nnb,
                          double *r2nn, int *status, int *ovf_list, hipStream_t s, int *nb_work) {
   if (ni <= 0) return hipSuccess;
-  if (ni <= kFewMaxNi && nsplit > 64 && nsplit <= 256 * kFewSplitsPerLane) {
-    hipLaunchKernelGGL(reduce_few_kernel, dim3(static_cast<unsigned>(ni)), dim3(256), 0, s, nsplit, ni, iperm, part,
-                       nn_r2, nn_slot, jindex, nb_count, nb_slot, nbl ? 1 : 0, acc, jerk, pot, nnb, r2nn, status,
-                       ovf_list, nb_work);
-    return hipGetLastError();
-  }
-  const int G = split_lanes(nsplit, ni);
-  int log2G = 0;
-  while ((1 << log2G) < G) ++log2G;
-  const long long waves = (ni + (64 >> log2G) - 1) / (64 >> log2G);
-  const long long lanes = waves * 64;
-  hipLaunchKernelGGL(reduce_kernel, dim3(static_cast<unsigned>((lanes + 255) / 256)), dim3(256), 0, s, nsplit, ni,
-                     log2G, iperm, part, nn_r2, nn_slot, jindex, nb_count, nb_slot, nbl ? 1 : 0, acc, jerk, pot,
-                     nnb, r2nn, status, ovf_list, nb_work);
+  const int l = split_log2rows(nsplit, ni, kReduceFill);
+  hipLaunchKernelGGL(reduce_kernel, dim3(static_cast<unsigned>((ni + (1LL << l) - 1) >> l)), dim3(256), 0, s, nsplit,
+                     ni, l, iperm, part, nn_slot, jindex, nb_count, nb_slot, nbl ? 1 : 0, acc, jerk, pot, nnb, r2nn,
+                     status, ovf_list, nb_work);
   return hipGetLastError();
 }
 

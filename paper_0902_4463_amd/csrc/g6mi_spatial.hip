@@ -389,20 +389,9 @@ __global__ __launch_bounds__(kWG, wide_waves<G6MI_PREC_DS>()) void force_spatial
   }
   w.resolve(jp, 0); // exact slots from the sorted records in global memory
 
-  const size_t ni = static_cast<size_t>(a.ni);
-  auto store = [&](int i, const Totals &t, float best, int bslot) {
-    double *p = a.part + static_cast<size_t>(blockIdx.y) * 7 * ni + i;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      p[d * ni] = t.acc[d];
-      p[(3 + d) * ni] = t.jrk[d];
-    }
-    p[6 * ni] = t.pot;
-    a.nn_r2[blockIdx.y * ni + i] = static_cast<double>(best);
-    a.nn_slot[blockIdx.y * ni + i] = bslot;
-  };
-  if (w.v0) store(q0, w.t0, w.ebest0, w.eslot0);
-  if (w.v1) store(q1, w.t1, w.ebest1, w.eslot1);
+  const size_t e0 = static_cast<size_t>(blockIdx.y) * a.ni;
+  if (w.v0) store_part(a.part, a.nn_slot, e0 + q0, w.t0, static_cast<double>(w.ebest0), w.eslot0);
+  if (w.v1) store_part(a.part, a.nn_slot, e0 + q1, w.t1, static_cast<double>(w.ebest1), w.eslot1);
 }
 
 // ---------------------------------------------------------------- launchers
