@@ -311,11 +311,14 @@ int ilog2(int v) {
 }
 
 // Launch shape.  i-particles per workgroup: 512 (two per lane) for blocks
-// of at least 512, else the smallest power of two covering the block, at
+// of at least 512, or 256 (one per lane, force_one) where that spreads or
+// hides latency better, else the smallest power of two covering the block, at
 // most 256 (one per lane); below 256 the spare lanes split the j-tile among
 // themselves (Sec. 2.3, Fig. accMP1).
-// j-splits: enough workgroups for G6MI_WG_PER_CU per compute unit (Sec. 2.3,
-// Fig. accGPU splits j over all multiprocessors), each split at least
+// j-splits (Sec. 2.3, Fig. accGPU splits j over all multiprocessors): where
+// the split boundaries do not enter the float32 sums (free_splits) as many as
+// the device needs, down to one tile each (fill_tiles, few_splits); else
+// enough workgroups for G6MI_WG_PER_CU per compute unit, each split at least
 // kMinTiles tiles long.  Many short workgroups keep the last round on each
 // CU small (measured: 8 splits of 2^20 j beat 1 split by 7%).
 #ifndef G6MI_WG_PER_CU
@@ -324,6 +327,66 @@ int ilog2(int v) {
 constexpr int kWaveTarget = G6MI_WG_PER_CU;
 constexpr int kMinTiles = 8;
 constexpr int kOneSplits = 256;
+
+// Whether a particle's float32 sums are the same wherever the j-range is cut
+// between tiles.  Blocks of 32 to 256 i-particles per workgroup fold a group
+// by its place in the split's nearest-neighbour search (fold_or_add), so
+// theirs are not; float64 sums, the sums of force_wide and force_one, and
+// blocks with at most one group per lane and tile are.
+bool free_splits(int prec, int ipw, bool one) {
+  return prec == G6MI_PREC_FP64 || ipw == 2 * kWG || one || ipw * kGroup <= kTile;
+}
+
+// Splits of a block of at most 256 i-particles with free splits: the float64
+// variant's larger blocks are bound by arithmetic and take four workgroups
+// per compute unit (100 i-particles against 2^20: 1024 splits 210 us, 512
+// 227 us), the others stream the j-memory (8 against 2^20: 512 splits 39 us,
+// 1024 44 us; one i-particle, 256 splits 25.3-26.3 us, 512 26.4-27.1 us,
+// whose reduction takes a second round of loads).
+int few_splits(int prec, int ipw) {
+  if (ipw == 1) return kOneSplits;
+  return prec == G6MI_PREC_FP64 && ipw * kGroup > kTile ? 1024 : 512;
+}
+
+// Tiles per split of force_one over nib i-blocks of 256 and ntiles tiles: the
+// choice with the least modelled time, in units of a tile's time with four
+// workgroups on each compute unit (53 us in double-single, 44 us in float32,
+// 88 us in float64).  Workgroups run in rounds of four per compute unit; a
+// last round of k per compute unit takes the fraction below of a full one
+// (latency-bound float32 variants gain little from fewer neighbours, float64
+// issue-bound almost in proportion; measured with one, two and four tiles
+// per split at N = 16384 .. 262144), and each workgroup costs about a tenth
+// of a tile besides.  The reduction reads 68 bytes per i-particle and split
+// at about 4.3 TB/s.
+int fill_tiles(int prec, int ncu, long ni, long nib, int ntiles) {
+  static const double part32[4] = {0.52, 0.62, 0.87, 1.0}, part64[4] = {0.33, 0.55, 0.85, 1.0};
+  const double *part = prec == G6MI_PREC_FP64 ? part64 : part32;
+  const double tile_us = prec == G6MI_PREC_FP64 ? 88.0 : (prec == G6MI_PREC_DS ? 53.0 : 44.0);
+  const long slots = 4L * ncu;
+  int best = 1;
+  double least = INFINITY;
+  for (int per = 1; per <= std::min(ntiles, 64); ++per) {
+    const long nsplit = (ntiles + per - 1) / per;
+    if (nsplit > 4096) continue;
+    const long wgs = nib * nsplit, rem = wgs % slots;
+    double t = static_cast<double>(wgs / slots) * (per + 0.1);
+    if (rem > 0) t += per * part[std::min(3L, (rem - 1) / ncu)] + 0.1;
+    t += static_cast<double>(nsplit) * ni * 68.0 / (4.3e6 * tile_us);
+    if (t < least) {
+      least = t;
+      best = per;
+    }
+  }
+  return std::isinf(least) ? (ntiles + 4095) / 4096 : best;
+}
+
+// From this many tiles times i-blocks of 256 on, two i-particles per lane
+// are the faster: float64 2^18 x 2^18 73.4 against 75.0 ms (2^20 tiles),
+// 16384 x 2^20 (2^18 tiles) level, 2048 x 2^18 655 against 646 us; double-
+// single 131072 x 2^20 (2^21 tiles) 93.4 against 94.6 ms, 16384 x 2^20 12.2
+// against 11.9 ms.  Float32 with one per lane is faster throughout (131072 x
+// 2^20 76.8 against 78.8 ms, 2048 x 2^18 366 against 407 us).
+constexpr long kWideTiles64 = 1L << 18, kWideTilesDS = 1L << 20;
 
 // Spatial ordering (g6mi_spatial.hip) for double-single blocks of at least
 // this many i-particles against at least two tiles (automatic mode).  The
@@ -347,29 +410,36 @@ bool use_fused(const Handle &h, bool spatial, int ipw, int ni, int nj) {
   return h.fuse && !spatial && ni > 0 && nj > 0 && ipw <= kWG && ni <= ipw;
 }
 
-void choose_shape(Handle &h, int ni, int nj, int &ipw, int &nsplit, bool may_order = true) {
+void choose_shape(Handle &h, int ni, int nj, int &ipw, int &nsplit, bool &one, bool may_order = true) {
   const int ntiles = (nj + kTile - 1) / kTile;
-  if (may_order && use_spatial(h, ni, nj)) ipw = 2 * kWG;
+  const int ncu = std::max(1, h.ncu);
+  const bool spatial = may_order && use_spatial(h, ni, nj);
+  one = false;
+  if (spatial) ipw = 2 * kWG;
   else if (h.user_ipw) ipw = h.user_ipw;
-  else if (ni >= 2 * kWG) ipw = 2 * kWG; // two i-particles per lane
-  else {
+  else if (ni >= 2 * kWG || (h.prec == G6MI_PREC_FP64 && ni > kWG)) {
+    const long tiles = static_cast<long>((ni + kWG - 1) / kWG) * ntiles;
+    one = h.prec == G6MI_PREC_FP32 || tiles < (h.prec == G6MI_PREC_FP64 ? kWideTiles64 : kWideTilesDS);
+    ipw = one ? kWG : 2 * kWG;
+  } else {
     ipw = kWG;
     while (ipw > 1 && ipw / 2 >= ni) ipw /= 2;
   }
   const long nib = (ni + ipw - 1) / ipw;
   if (h.user_nsplit) {
     nsplit = std::max(1, std::min(h.user_nsplit, std::max(1, ntiles)));
+  } else if (one && ntiles > 0) {
+    const int per = fill_tiles(h.prec, ncu, ni, nib, ntiles);
+    nsplit = (ntiles + per - 1) / per;
+  } else if (ipw < 2 * kWG && nib == 1 && ntiles > 0 && free_splits(h.prec, ipw, one)) {
+    const int most = few_splits(h.prec, ipw), per = (ntiles + most - 1) / most;
+    nsplit = (ntiles + per - 1) / per;
   } else {
     // enough workgroups that the last round on each compute unit is a small
     // fraction of the work, each split at least kMinTiles tiles long
-    const long target = static_cast<long>(kWaveTarget) * std::max(1, h.ncu);
+    const long target = static_cast<long>(kWaveTarget) * ncu;
     nsplit = static_cast<int>(std::max(1L, (target + nib - 1) / std::max(1L, nib)));
     nsplit = std::max(1, std::min(nsplit, std::max(1, ntiles / kMinTiles)));
-    // one particle with the predictor fused in: the interaction streams the
-    // j-memory whatever the split count, and the reduction of 256 splits
-    // takes one round of loads where 512 take two (measured at 2^20 j:
-    // 25.3-26.3 against 26.4-27.1 us per call)
-    if (ipw == 1 && h.fuse) nsplit = std::min(nsplit, kOneSplits);
   }
   nsplit = std::min(nsplit, 4096);
 }
@@ -512,10 +582,11 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
     if (rc) return rc;
   }
   int ipw, nsplit;
-  choose_shape(h, ni, nj, ipw, nsplit, !noalloc);
+  bool one;
+  choose_shape(h, ni, nj, ipw, nsplit, one, !noalloc);
   const bool spatial = !noalloc && use_spatial(h, ni, nj);
   // one i-block of at most kWG: the interaction kernel predicts its tiles
-  const bool fused = use_fused(h, spatial, ipw, ni, nj);
+  const bool fused = !one && use_fused(h, spatial, ipw, ni, nj);
   CalcBufs c;
   if (noalloc) {
     while (nsplit > 1 && calc_bytes(h.prec, fused, nj, ni, nsplit) > scratch_bytes) nsplit = (nsplit + 1) / 2;
@@ -564,6 +635,7 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
   a.eps2 = eps2;
   a.ipw = ipw;
   a.log2ipw = ilog2(ipw);
+  a.one = one ? 1 : 0;
   a.part = c.part;
   a.nn_slot = c.nnslot;
   a.nb_count = c.nbcount;

@@ -15,9 +15,6 @@
 
 namespace g6mi {
 
-// j-records per group: the unit of the nearest-neighbour bookkeeping, of the
-// neighbour-list flags and of the first level of float32 summation.
-constexpr int kGroup = G6MI_GROUP;
 // Group length of the spatially ordered kernel (force_spatial).  Nine tiles
 // in ten are far there, their pair terms within a small factor of each
 // other, and the near tiles fold every group into float64; a longer group
@@ -776,8 +773,13 @@ struct WideLanes {
 // (Sec. 2.3, Fig. accMP1: spare threads split the j-range).  Full tiles
 // without an own slot use the grouped path of WideLanes with stride-L
 // groups.
-template <int PREC, bool NBL>
+// WIDE: the sums are grouped as in WideLanes (DS: every group straight into
+// the float64 totals; FP32: group sums into the tile sums) instead of by
+// fold_or_add, for force_one, which serves the blocks of force_wide with one
+// i-particle per lane and gives the same float32 sums.
+template <int PREC, bool NBL, bool WIDE = false>
 struct NarrowLane {
+  static constexpr bool kFold = WIDE && PREC == G6MI_PREC_DS;
   using R = real_t<PREC>;
   static constexpr int REC = rec4<PREC>();
   IState<PREC> st;
@@ -812,7 +814,7 @@ struct NarrowLane {
     if (cnt < kTile || K < kGroup) {
       int *nb_cnt = nb_count + (valid ? row : 0);
       int *nb_row = nb_slot + static_cast<size_t>(valid ? row : 0) * kNbMax;
-      MaskedRun<PREC, NBL, false, true> run;
+      MaskedRun<PREC, NBL, kFold, !WIDE> run;
       run.start();
       for (int jj = sub; jj < cnt; jj += L)
         run.step(st, ts, t, tl + jj * REC, jbase + jj, slot, eps2, h2, ebest, eslot, nb_cnt, nb_row);
@@ -847,7 +849,8 @@ struct NarrowLane {
           const int jj = sub + ((k0 + u) << log2L);
           m = fmin(m, pair_core<PREC, false, SELF>(st, gs, tl + jj * REC, eps2, jj == o));
         }
-        if constexpr (G6MI_NARROW_FOLD) fold(gs, t);
+        if constexpr (kFold || G6MI_NARROW_FOLD) fold(gs, t);
+        else if constexpr (WIDE) ts.add(gs);
         else fold_or_add(gs, ts, t, m < gbest);
       }
       if (m < gbest) {

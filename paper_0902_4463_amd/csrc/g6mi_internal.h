@@ -45,6 +45,9 @@ namespace g6mi {
 
 constexpr int kWG = 256;          // lanes per workgroup: four wave64
 constexpr int kTile = G6MI_TILE;  // j-records staged in LDS per tile
+// j-records per group: the unit of the nearest-neighbour bookkeeping, of the
+// neighbour-list flags and of the first level of float32 summation.
+constexpr int kGroup = G6MI_GROUP;
 constexpr int kNbMax = 256;       // neighbour slots per i-particle
 constexpr int kFusedDepth = G6MI_FUSED_DEPTH;
 constexpr int kPartDoubles = 8;   // doubles per row of a split partial (see store_part)
@@ -83,6 +86,7 @@ struct ForceArgs {
   double eps2 = 0.0;
   int ipw = kWG;               // i-particles per workgroup, power of two
   int log2ipw = 8;
+  int one = 0;                 // ipw = kWG: force_one (the sums of force_wide)
   // outputs of the j-split s in [0, nsplit):
   double *part = nullptr;      // [nsplit][ni][kPartDoubles]: acc xyz, jerk xyz, sum m/r, neighbour r^2
   int *nn_slot = nullptr;      // [nsplit][ni]

@@ -182,6 +182,55 @@ __global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a) {
     store_part(a.part, a.nn_slot, static_cast<size_t>(blockIdx.y) * a.ni + i, n.t, bestd, bslot);
 }
 
+// The blocks of force_wide with one i-particle per lane, 256 per workgroup
+// (NarrowLane with WIDE sums): half the i-particles and half the work per
+// workgroup and tile, and waves without an i-particle skip the tiles, so
+// blocks of a few hundred to a few thousand i-particles, whose tiles would
+// not fill the compute units evenly in workgroups of 512, spread better; four
+// workgroups fit a compute unit (three of force_wide).  The float32 sums are
+// those of force_wide.  785 i-particles against 2^17 in float32: 102 us with
+// one to four tiles per split, 300 us as force_wide in 128 workgroups of
+// eight tiles; 2048 against 2^18, same splits: 366 against 407 us (double-
+// single 438 against 476).
+template <int PREC, bool NBL>
+__global__ __launch_bounds__(kWG, 4) void force_one(ForceArgs a) {
+  constexpr int REC = rec4<PREC>();
+  constexpr int kLoads = kTile * REC / kWG;
+  __shared__ __attribute__((aligned(16))) float4 tile[kTile * REC];
+
+  const int tid = threadIdx.x;
+  const int i = blockIdx.x * kWG + tid;
+  NarrowLane<PREC, NBL, true> n;
+  n.init(a, i, i < a.ni, 0, 0);
+  const real_t<PREC> eps2 = static_cast<real_t<PREC>>(a.eps2);
+
+  const int ntiles = (a.nj + kTile - 1) / kTile;
+  const int per = (ntiles + gridDim.y - 1) / gridDim.y;
+  const int tb = blockIdx.y * per;
+  const int te = min(ntiles, tb + per);
+  const float4 *jp = static_cast<const float4 *>(a.jpred);
+  const bool busy = __any(n.valid);
+
+  TileRegs<kLoads> nxt;
+  if (tb < te) nxt.load(jp + static_cast<size_t>(tb) * kTile * REC, tid, min(kTile, a.nj - tb * kTile) * REC);
+  for (int tt = tb; tt < te; ++tt) {
+    const int jbase = tt * kTile;
+    const int cnt = min(kTile, a.nj - jbase);
+    __syncthreads();
+    nxt.store(tile, tid, cnt * REC);
+    {
+      const int tn = min(tt + 1, te - 1); // the last tile loads itself again
+      nxt.load(jp + static_cast<size_t>(tn) * kTile * REC, tid, min(kTile, a.nj - tn * kTile) * REC);
+    }
+    __syncthreads();
+    if (busy) n.tile(tile, jbase, cnt, eps2, a.nb_count, a.nb_slot);
+  }
+  n.resolve(jp, 0); // exact slots from the records in global memory, as in force_wide
+  if (n.valid)
+    store_part(a.part, a.nn_slot, static_cast<size_t>(blockIdx.y) * a.ni + i, n.t, static_cast<double>(n.ebest),
+               n.eslot);
+}
+
 // ------------------------------------ small blocks, predictor fused in
 
 // A block of at most 256 i-particles (one i-block, NarrowLane as in
@@ -487,7 +536,12 @@ hipError_t launch_predict(int prec, int nj, double ti, const JMem &jm, void *out
 
 template <int PREC>
 static void launch_force_prec(bool nbl, const ForceArgs &a, dim3 grid, hipStream_t s) {
-  if (a.ipw == 2 * kWG) {
+  if (a.one) {
+    if (nbl)
+      hipLaunchKernelGGL((force_one<PREC, true>), grid, dim3(kWG), 0, s, a);
+    else
+      hipLaunchKernelGGL((force_one<PREC, false>), grid, dim3(kWG), 0, s, a);
+  } else if (a.ipw == 2 * kWG) {
     if (nbl)
       hipLaunchKernelGGL((force_wide<PREC, true>), grid, dim3(kWG), 0, s, a);
     else

@@ -1,0 +1,65 @@
+"""Launch shapes chosen by the library against shapes set by hand that take
+the general kernels: where a split of the j-range or the i-particles per lane
+must not change the float32 sums, the results differ only by the order of the
+float64 additions above them."""
+
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+# at most about 10^4 float64 additions in another order, of terms whose sum
+# cancels by less than 10^3: 10^4 * 10^3 * 1e-16
+RTOL = 1e-9
+
+
+def evaluate(g6, s, jm, slots, xi, vi, eps2, h2, shape):
+    g6.check(s.id, g6.g6mi_set_shape(s.id, *shape))
+    return s.calc(jm.n, jm.meta["ti"], jm.index[slots], xi, vi, eps2, h2)
+
+
+def assert_same_sums(a, b):
+    for k in ("acc", "jerk", "pot"):
+        d = np.linalg.norm((a[k] - b[k]).reshape(len(a[k]), -1), axis=1)
+        assert np.all(d <= RTOL * np.linalg.norm(b[k].reshape(len(b[k]), -1), axis=1)), k
+    for k in ("nn_index", "nn_r2", "nb_count", "nb_list"):
+        assert np.array_equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("prec", ["ds", "fp32", "fp64"])
+@pytest.mark.parametrize("n,ni", [(700, 512), (600, 600), (2049, 513), (4096, 767), (20001, 1025), (70000, 3000)])
+def test_one_particle_per_lane_matches_two(prec, n, ni):
+    """force_one (chosen from 512 i-particles on; float64 from 257) against
+    force_wide (512 i-particles per workgroup asked for)."""
+    import paper_0902_4463_amd as g6
+    jm = workloads.random_cluster(n, seed=4000 + n)
+    slots = workloads.active_set(n, ni, seed=ni)
+    with g6.Session(4, precision=prec) as s:
+        s.load(jm)
+        xi, vi = jm.x[slots], jm.v[slots]
+        a = evaluate(g6, s, jm, slots, xi, vi, 1e-4, 0.02, (0, 0))
+        assert g6.g6mi_get_shape(s.id)["i_per_group"] == 256
+        b = evaluate(g6, s, jm, slots, xi, vi, 1e-4, 0.02, (512, 3))
+        assert g6.g6mi_get_shape(s.id)["i_per_group"] == 512
+    assert_same_sums(a, b)
+
+
+@pytest.mark.parametrize("prec,ni", [("ds", 1), ("ds", 2), ("ds", 9), ("ds", 16), ("fp32", 16), ("fp64", 1),
+                                     ("fp64", 33), ("fp64", 256), ("fp64", 257), ("fp64", 400)])
+@pytest.mark.parametrize("n", [1, 256, 257, 5000])
+def test_split_count_of_small_blocks(prec, ni, n):
+    """The chosen split count (down to one tile per split) against one
+    split."""
+    import paper_0902_4463_amd as g6
+    jm = workloads.random_cluster(n, seed=4100 + n)
+    rng = np.random.default_rng(ni)
+    slots = np.sort(rng.permutation(n)[:ni]) if ni <= n else rng.integers(0, n, ni)
+    with g6.Session(4, precision=prec) as s:
+        s.load(jm)
+        xi, vi = jm.x[slots], jm.v[slots]
+        a = evaluate(g6, s, jm, slots, xi, vi, 1e-4, 0.02, (0, 0))
+        b = evaluate(g6, s, jm, slots, xi, vi, 1e-4, 0.02, (0, 1))
+        assert g6.g6mi_get_shape(s.id)["j_splits"] == 1
+    assert_same_sums(a, b)
