@@ -113,7 +113,7 @@ struct Handle {
   PinBuf h_i, h_out;
 
   // work buffers
-  DevBuf d_part, d_nnslot, d_nbcount, d_nblist, d_flags, d_ovf;
+  DevBuf d_part, d_min, d_nnslot, d_nbcount, d_nblist, d_flags, d_ovf;
   // neighbour counters of the fused path: all zero between calculations
   // (each reduction clears the rows it used); nbwork_ok is false until a
   // new buffer has been cleared or after a calculation that did not reach
@@ -444,6 +444,23 @@ void choose_shape(Handle &h, int ni, int nj, int &ipw, int &nsplit, bool &one, b
   nsplit = std::min(nsplit, 4096);
 }
 
+// Tiles per piece (PieceArgs) of a block whose split boundaries are fixed
+// (!free_splits) and whose nsplit splits over nib i-blocks make fewer than
+// two workgroups per compute unit, or 0: pieces as short as four workgroups
+// per compute unit allow.  Measured: 341 i-particles against 2^15 in
+// double-single 258 us of kernels in 16 splits of eight tiles, 52 us in 128
+// pieces of one; with two workgroups per compute unit (100 against 2^20)
+// the minima cost as much as the pieces gain.
+int piece_tiles(const Handle &h, int ipw, bool one, bool spatial, int ni, int nj, int nsplit) {
+  if (spatial || ni <= 0 || nj <= 0 || h.user_ipw || h.user_nsplit || ipw > kWG || free_splits(h.prec, ipw, one))
+    return 0;
+  const long ncu = std::max(1, h.ncu), nib = (ni + ipw - 1) / ipw, ntiles = (nj + kTile - 1) / kTile;
+  const long vper = (ntiles + nsplit - 1) / nsplit;
+  if (nib * nsplit >= 2 * ncu || vper < 2) return 0;
+  const long per = (nib * ntiles + 4 * ncu - 1) / (4 * ncu);
+  return static_cast<int>(std::min(per, vper));
+}
+
 // Buffers of the spatial ordering for nj records and ni i-particles.
 int ensure_spatial(Handle &h, int nj, int ni) {
   const size_t n = static_cast<size_t>(std::max(nj, ni)), j = static_cast<size_t>(nj), i = static_cast<size_t>(ni);
@@ -491,6 +508,7 @@ struct CalcBufs {
   int *nnslot = nullptr;
   int *nbcount = nullptr, *nblist = nullptr;
   int *flags = nullptr, *ovf = nullptr;    // status words, overflow queue
+  float *least = nullptr, *exact = nullptr; // minima of a calculation in pieces
   int *nbwork = nullptr;                   // fused kernel's neighbour counters
   int nbwork_n = 0;                        // ... their number
   bool nbwork_zero = false;                // nbwork is known to be all zero
@@ -498,7 +516,8 @@ struct CalcBufs {
 
 // Bytes of the work buffers of a calculation of shape (ipw, nsplit) over
 // nj j-slots and ni i-particles, in the order and alignment of carve_bufs.
-size_t calc_bytes(int prec, bool fused, int nj, int ni, int nsplit) {
+// nmin: minima of a calculation in pieces (0: none).
+size_t calc_bytes(int prec, bool fused, int nj, int ni, int nsplit, size_t nmin) {
   const size_t n = static_cast<size_t>(std::max(ni, 1)), ns = static_cast<size_t>(nsplit);
   size_t b = 0;
   auto add = [&](size_t x) { b += round_up(x, 256); };
@@ -510,11 +529,12 @@ size_t calc_bytes(int prec, bool fused, int nj, int ni, int nsplit) {
   add(64);
   add(2 * n * sizeof(int));
   add(fused ? n * sizeof(int) : 0);
+  add(2 * nmin * sizeof(float));
   return b;
 }
 
 // The same buffers cut from one region of at least calc_bytes bytes.
-CalcBufs carve_bufs(void *base, int prec, bool fused, int nj, int ni, int nsplit) {
+CalcBufs carve_bufs(void *base, int prec, bool fused, int nj, int ni, int nsplit, size_t nmin) {
   const size_t n = static_cast<size_t>(std::max(ni, 1)), ns = static_cast<size_t>(nsplit);
   char *p = static_cast<char *>(base);
   auto take = [&](size_t x) {
@@ -532,12 +552,14 @@ CalcBufs carve_bufs(void *base, int prec, bool fused, int nj, int ni, int nsplit
   c.ovf = static_cast<int *>(take(2 * n * sizeof(int)));
   c.nbwork = fused ? static_cast<int *>(take(n * sizeof(int))) : nullptr;
   c.nbwork_n = fused ? static_cast<int>(n) : 0;
+  c.least = static_cast<float *>(take(2 * nmin * sizeof(float)));
+  c.exact = c.least + nmin;
   if (fused) c.pred = nullptr;
   return c;
 }
 
 // The handle's own work buffers, grown as needed.
-int handle_bufs(Handle &h, bool fused, int nj, int ni, int nsplit, CalcBufs &c) {
+int handle_bufs(Handle &h, bool fused, int nj, int ni, int nsplit, size_t nmin, CalcBufs &c) {
   const size_t n = static_cast<size_t>(std::max(ni, 1));
   if (!fused) HIPCHK(&h, ensure(h.d_pred, std::max<size_t>(1, nj) * pred_record_bytes(h.prec)));
   HIPCHK(&h, ensure(h.d_part, static_cast<size_t>(nsplit) * n * kPartDoubles * sizeof(double)));
@@ -553,6 +575,11 @@ int handle_bufs(Handle &h, bool fused, int nj, int ni, int nsplit, CalcBufs &c) 
   c.nblist = static_cast<int *>(h.d_nblist.p);
   c.flags = static_cast<int *>(h.d_flags.p);
   c.ovf = static_cast<int *>(h.d_ovf.p);
+  if (nmin) {
+    HIPCHK(&h, ensure(h.d_min, 2 * nmin * sizeof(float)));
+    c.least = static_cast<float *>(h.d_min.p);
+    c.exact = c.least + nmin;
+  }
   if (fused) {
     const size_t before = h.d_nbwork.bytes;
     HIPCHK(&h, ensure(h.d_nbwork, n * sizeof(int)));
@@ -585,18 +612,34 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
   bool one;
   choose_shape(h, ni, nj, ipw, nsplit, one, !noalloc);
   const bool spatial = !noalloc && use_spatial(h, ni, nj);
+  PieceArgs pc;
+  pc.per = piece_tiles(h, ipw, one, spatial, ni, nj, nsplit);
+  const int ntiles = (nj + kTile - 1) / kTile;
+  const size_t nib = static_cast<size_t>((ni + ipw - 1) / ipw), minima = nib * ntiles * kWG;
+  if (pc.per) {
+    pc.vper = (ntiles + nsplit - 1) / nsplit;
+    pc.vlast = (ntiles - 1) / pc.vper * pc.vper;
+    const int npieces = (ntiles + pc.vper - 1) / pc.vper * ((pc.vper + pc.per - 1) / pc.per);
+    // the static scratch array too small for the pieces: whole splits
+    if (noalloc && calc_bytes(h.prec, false, nj, ni, npieces, minima) > scratch_bytes) pc = PieceArgs{};
+    else nsplit = npieces;
+  }
   // one i-block of at most kWG: the interaction kernel predicts its tiles
-  const bool fused = !one && use_fused(h, spatial, ipw, ni, nj);
+  const bool fused = !one && !pc.per && use_fused(h, spatial, ipw, ni, nj);
+  const size_t nmin = pc.per ? minima : 0;
   CalcBufs c;
   if (noalloc) {
-    while (nsplit > 1 && calc_bytes(h.prec, fused, nj, ni, nsplit) > scratch_bytes) nsplit = (nsplit + 1) / 2;
-    if (calc_bytes(h.prec, fused, nj, ni, nsplit) > scratch_bytes)
+    while (!pc.per && nsplit > 1 && calc_bytes(h.prec, fused, nj, ni, nsplit, 0) > scratch_bytes)
+      nsplit = (nsplit + 1) / 2;
+    if (calc_bytes(h.prec, fused, nj, ni, nsplit, nmin) > scratch_bytes)
       return fail(&h, G6MI_EINVAL, "calculation too large for the static scratch buffer (nj or ni too large)");
-    c = carve_bufs(scratch, h.prec, fused, nj, ni, nsplit);
+    c = carve_bufs(scratch, h.prec, fused, nj, ni, nsplit, nmin);
   } else {
-    int rc = handle_bufs(h, fused, nj, ni, nsplit, c);
+    int rc = handle_bufs(h, fused, nj, ni, nsplit, nmin, c);
     if (rc) return rc;
   }
+  pc.least = c.least;
+  pc.exact = nj % kTile ? c.exact : nullptr;
   int *status = c.flags; // cleared by the predictor launch, or by force_fused
 
   h.shape[0] = ipw;
@@ -621,7 +664,7 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
     if (!noalloc) h.nbwork_ok = false; // until the reduction is enqueued
   }
   if (ev) HIPCHK(&h, hipEventRecord(ev[0], s));
-  if (!fused) HIPCHK(&h, launch_predict(h.prec, nj, h.ti, h.jm, c.pred, c.nbcount, ni, status, s));
+  if (!fused && !pc.per) HIPCHK(&h, launch_predict(h.prec, nj, h.ti, h.jm, c.pred, c.nbcount, ni, status, s));
   if (spatial) HIPCHK(&h, launch_spatial_prep(h.sp, nj, ni, c.pred, d_xi, d_vi, d_h2, d_islot, s));
   if (ev) HIPCHK(&h, hipEventRecord(ev[1], s));
   ForceArgs a;
@@ -642,6 +685,8 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
   a.nb_slot = c.nblist;
   if (spatial) {
     HIPCHK(&h, launch_force_spatial(h.nbl, a, h.sp, nsplit, s));
+  } else if (pc.per) {
+    HIPCHK(&h, launch_force_pieces(h.prec, h.nbl, a, h.jm, h.ti, pc, c.pred, status, nsplit, s));
   } else if (fused) {
     HIPCHK(&h, launch_force_fused(h.prec, h.nbl, a, h.jm, h.ti, c.nbwork, status, nsplit, s));
   } else {
@@ -1087,7 +1132,7 @@ G6MI_API int g6_close(int id) {
   for (DevBuf *b : {&h->hs.d_ctl, &h->hs.d_state, &h->hs.d_block}) b->release();
   h->hs.h_ctl.release();
   for (DevBuf *b : {&h->d_jm, &h->d_pred, &h->d_stage, &h->d_i, &h->d_out, &h->d_part,
-                    &h->d_nnslot, &h->d_nbcount, &h->d_nblist, &h->d_flags,
+                    &h->d_min, &h->d_nnslot, &h->d_nbcount, &h->d_nblist, &h->d_flags,
                     &h->d_ovf, &h->d_cl, &h->d_plan, &h->d_items, &h->d_bwork, &h->d_ibcl, &h->d_sp})
     b->release();
   for (PinBuf *b : {&h->h_stage, &h->h_i, &h->h_out, &h->h_cl}) b->release();

@@ -101,6 +101,22 @@ hipError_t launch_predict(int prec, int nj, double ti, const JMem &jm,
 hipError_t launch_force(int prec, bool nbl, const ForceArgs &a, int nsplit,
                         hipStream_t s);
 
+// A calculation of small blocks in pieces of its j-splits (piece_min_kernel,
+// then force_kernel): splits of vper tiles in pieces of per tiles, so that a
+// j-range too short for many splits still fills the device.  vlast: first
+// tile of the last split.
+struct PieceArgs {
+  int vper = 0, per = 0, vlast = 0;
+  float *least = nullptr; // [tile][i-block][kWG] least softened r^2 of a lane in a tile
+  float *exact = nullptr; // the same shape: exact r^2 of that group (nj not a multiple of kTile), or null
+};
+
+// Predictor and minima, then the interaction over npieces = (splits) *
+// ceil(vper / per) pieces, whose partials the reduction adds as so many
+// splits.  double-single and float32.
+hipError_t launch_force_pieces(int prec, bool nbl, const ForceArgs &a, const JMem &jm, double ti,
+                               const PieceArgs &pc, void *jpred, int *status, int npieces, hipStream_t s);
+
 // One i-block of at most kWG i-particles (a.ipw <= kWG) with the predictor
 // fused into the tile load: reads the j-memory jm at time ti instead of
 // a.jpred, counts neighbours in nb_work (all zero before the launch; the

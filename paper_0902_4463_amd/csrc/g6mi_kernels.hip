@@ -126,14 +126,90 @@ template <int K> struct TileRegs {
   }
 };
 
+// First launch of a calculation in pieces (PieceArgs): the predictor, and
+// each lane's least softened r^2 in each tile.  Where a group is folded into
+// the float64 totals depends on the least r^2 that the lane met before it in
+// its split (fold_or_add), so a split of eight or more tiles is one serial
+// chain; with the minima of its earlier tiles known, every piece of a split
+// can start on its own and make the same decisions.  The minima take a third
+// of the operations of the full pair.
+// Workgroup (x, y): i-block x, tile y.  i-block 0 writes the predicted
+// records; the tiles of a split's last piece need no minima.  For the split
+// that holds the ragged tile, whose lanes go by the exact r^2 found so far
+// (MaskedRun), the exact r^2 of the group holding the minimum is kept too:
+// the group that NarrowLane would resolve after the tile if it lies below
+// the minima before.  The same launch clears the neighbour counters and
+// status words.
+template <int PREC>
+__global__ __launch_bounds__(kWG) void piece_min_kernel(ForceArgs a, JMem jm, double ti, PieceArgs pc,
+                                                        float4 *__restrict__ jpred, int *__restrict__ status) {
+  static_assert(PREC != G6MI_PREC_FP64, "float64 sums do not depend on the splits");
+  constexpr int REC = rec4<PREC>();
+  __shared__ __attribute__((aligned(16))) float4 tile[kTile * REC];
+  const int tid = threadIdx.x, tt = blockIdx.y;
+  const int il = tid & (a.ipw - 1), i = blockIdx.x * a.ipw + il;
+  if (tt == 0) {
+    if (blockIdx.x == 0 && tid < kStatusWords) status[tid] = 0;
+    if (tid < a.ipw && i < a.ni) a.nb_count[i] = 0;
+  }
+  const int jbase = tt * kTile, cnt = min(kTile, a.nj - jbase);
+  const int pos = tt % pc.vper;
+  const int len = min(pc.vper, (a.nj + kTile - 1) / kTile - (tt - pos)); // tiles of the split
+  const bool need = pos / pc.per < (len - 1) / pc.per;                   // a later piece follows
+  if (blockIdx.x > 0 && !need) return;
+  if (tid < cnt) {
+    predict_record<PREC>(jm, static_cast<size_t>(jbase + tid), ti, tile + tid * REC);
+    if (blockIdx.x == 0)
+#pragma unroll
+      for (int q = 0; q < REC; ++q) jpred[static_cast<size_t>(jbase + tid) * REC + q] = tile[tid * REC + q];
+  }
+  if (!need) return;
+  IState<PREC> st;
+  int slot;
+  float h2;
+  load_i<PREC>(st, a, i, i < a.ni, slot, h2);
+  __syncthreads();
+  if (!__any(i < a.ni)) return;
+  // a tile with a later piece is full
+  const int log2L = 8 - a.log2ipw, sub = tid >> a.log2ipw, own = slot - jbase;
+  const float eps2 = static_cast<float>(a.eps2);
+  float best = INFINITY;
+  int grp = -1;
+  for (int k0 = 0; k0 < kTile >> log2L; k0 += kGroup) {
+    float m = INFINITY;
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) {
+      const int jj = sub + ((k0 + u) << log2L);
+      float d[3], w[3], mj;
+      separation<PREC>(st, tile + jj * REC, d, w, mj);
+      const float s = fma(d[2], d[2], fma(d[1], d[1], fma(d[0], d[0], eps2))); // as in pair_core
+      m = fmin(m, jj == own ? INFINITY : s);
+    }
+    if (m < best) {
+      best = m;
+      grp = jbase + sub + (k0 << log2L);
+    }
+  }
+  const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + tid;
+  pc.least[e] = best;
+  if (pc.exact && tt - pos == pc.vlast) {
+    float r2 = INFINITY;
+    int bs = -1;
+    resolve_group<PREC>(st, grp, 1 << log2L, tile, jbase, r2, bs, slot);
+    pc.exact[e] = r2;
+  }
+}
+
 // Small blocks (NarrowLane): ipw i-particles per workgroup (a power of two,
 // at most 256) and L = 256 / ipw lanes per i-particle; lane tid handles
 // i-particle (tid mod ipw) and the records sub, sub + L, ... of every tile,
 // sub = tid / ipw.  For ipw >= 64 every lane of a wave reads the same record
 // (an LDS broadcast).  The L lane totals of an i-particle are added in a
-// fixed order.  Grid: x = i-blocks, y = j-splits.
-template <int PREC, bool NBL>
-__global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a) {
+// fixed order.  Grid: x = i-blocks, y = j-splits, or (PIECES) the pieces of
+// the j-splits one split after the other, each starting from the minima of
+// its split's earlier tiles that piece_min_kernel found.
+template <int PREC, bool NBL, bool PIECES = false>
+__global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a, PieceArgs pc) {
   constexpr int REC = rec4<PREC>();
   constexpr int kLoads = kTile * REC / kWG;
   __shared__ __attribute__((aligned(16))) unsigned char lds[narrow_lds_bytes<PREC>()];
@@ -148,10 +224,27 @@ __global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a) {
   const real_t<PREC> eps2 = static_cast<real_t<PREC>>(a.eps2);
 
   const int ntiles = (a.nj + kTile - 1) / kTile;
-  const int per = (ntiles + gridDim.y - 1) / gridDim.y;
-  const int tb = blockIdx.y * per;
-  const int te = min(ntiles, tb + per);
   const float4 *jp = static_cast<const float4 *>(a.jpred);
+  int tb, te;
+  if constexpr (PIECES) {
+    const int ppv = (pc.vper + pc.per - 1) / pc.per; // pieces per split
+    const int v0 = static_cast<int>(blockIdx.y) / ppv * pc.vper;
+    tb = v0 + static_cast<int>(blockIdx.y) % ppv * pc.per;
+    te = min(min(ntiles, v0 + pc.vper), tb + pc.per);
+    for (int tt = v0; tt < min(tb, te); ++tt) {
+      const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + tid;
+      const float m = pc.least[e];
+      if (m < n.gbest) {
+        n.gbest = m;
+        if (pc.exact && v0 == pc.vlast) n.ebest = fminf(n.ebest, pc.exact[e]);
+      }
+    }
+  } else {
+    const int per = (ntiles + gridDim.y - 1) / gridDim.y;
+    tb = blockIdx.y * per;
+    te = min(ntiles, tb + per);
+  }
+  const bool busy = !PIECES || __any(n.valid); // whole waves without an i-particle have no work
 
   // The next tile's records are loaded into registers while the current
   // one is evaluated: a block of few i-particles spends little time per
@@ -168,11 +261,13 @@ __global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a) {
       nxt.load(jp + static_cast<size_t>(tn) * kTile * REC, tid, min(kTile, a.nj - tn * kTile) * REC);
     }
     __syncthreads();
-    n.tile(tile, jbase, cnt, eps2, a.nb_count, a.nb_slot);
-    // while the tile is still in LDS: the exact nearest neighbour so far
-    // decides which groups of a ragged tile fold into float64 (fold_or_add),
-    // as in force_fused and the batched kernel
-    n.resolve(tile, jbase);
+    if (busy) {
+      n.tile(tile, jbase, cnt, eps2, a.nb_count, a.nb_slot);
+      // while the tile is still in LDS: the exact nearest neighbour so far
+      // decides which groups of a ragged tile fold into float64 (fold_or_add),
+      // as in force_fused and the batched kernel
+      n.resolve(tile, jbase);
+    }
   }
 
   double bestd;
@@ -547,9 +642,9 @@ static void launch_force_prec(bool nbl, const ForceArgs &a, dim3 grid, hipStream
     else
       hipLaunchKernelGGL((force_wide<PREC, false>), grid, dim3(kWG), 0, s, a);
   } else if (nbl)
-    hipLaunchKernelGGL((force_kernel<PREC, true>), grid, dim3(kWG), 0, s, a);
+    hipLaunchKernelGGL((force_kernel<PREC, true>), grid, dim3(kWG), 0, s, a, PieceArgs{});
   else
-    hipLaunchKernelGGL((force_kernel<PREC, false>), grid, dim3(kWG), 0, s, a);
+    hipLaunchKernelGGL((force_kernel<PREC, false>), grid, dim3(kWG), 0, s, a, PieceArgs{});
 }
 
 hipError_t launch_force(int prec, bool nbl, const ForceArgs &a, int nsplit, hipStream_t s) {
@@ -560,6 +655,30 @@ hipError_t launch_force(int prec, bool nbl, const ForceArgs &a, int nsplit, hipS
   case G6MI_PREC_DS: launch_force_prec<G6MI_PREC_DS>(nbl, a, grid, s); break;
   default: launch_force_prec<G6MI_PREC_FP64>(nbl, a, grid, s);
   }
+  return hipGetLastError();
+}
+
+template <int PREC>
+static void launch_pieces_prec(bool nbl, const ForceArgs &a, const JMem &jm, double ti, const PieceArgs &pc,
+                               void *jpred, int *status, int npieces, hipStream_t s) {
+  const unsigned nib = static_cast<unsigned>((a.ni + a.ipw - 1) / a.ipw);
+  const unsigned ntiles = static_cast<unsigned>((a.nj + kTile - 1) / kTile);
+  hipLaunchKernelGGL(piece_min_kernel<PREC>, dim3(nib, ntiles), dim3(kWG), 0, s, a, jm, ti, pc,
+                     static_cast<float4 *>(jpred), status);
+  const dim3 grid(nib, static_cast<unsigned>(npieces));
+  if (nbl)
+    hipLaunchKernelGGL((force_kernel<PREC, true, true>), grid, dim3(kWG), 0, s, a, pc);
+  else
+    hipLaunchKernelGGL((force_kernel<PREC, false, true>), grid, dim3(kWG), 0, s, a, pc);
+}
+
+hipError_t launch_force_pieces(int prec, bool nbl, const ForceArgs &a, const JMem &jm, double ti,
+                               const PieceArgs &pc, void *jpred, int *status, int npieces, hipStream_t s) {
+  if (a.ni <= 0 || a.nj <= 0 || a.ipw > kWG || a.ipw < 1 || pc.per < 1 || pc.vper < pc.per || !pc.least)
+    return hipErrorInvalidValue;
+  if (prec == G6MI_PREC_DS) launch_pieces_prec<G6MI_PREC_DS>(nbl, a, jm, ti, pc, jpred, status, npieces, s);
+  else if (prec == G6MI_PREC_FP32) launch_pieces_prec<G6MI_PREC_FP32>(nbl, a, jm, ti, pc, jpred, status, npieces, s);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

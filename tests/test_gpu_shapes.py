@@ -63,3 +63,30 @@ def test_split_count_of_small_blocks(prec, ni, n):
         b = evaluate(g6, s, jm, slots, xi, vi, 1e-4, 0.02, (0, 1))
         assert g6.g6mi_get_shape(s.id)["j_splits"] == 1
     assert_same_sums(a, b)
+
+
+@pytest.mark.parametrize("prec", ["ds", "fp32"])
+@pytest.mark.parametrize("ni", [17, 33, 100, 256, 300, 511])
+@pytest.mark.parametrize("n", [257, 600, 1024, 4097, 5100, 33000])
+def test_pieces_match_whole_splits(prec, ni, n):
+    """Blocks of 17 to 511 in pieces of their j-splits, each starting from the
+    minima of its split's earlier tiles, against the same splits walked whole
+    (a shape set by hand).  Ragged last tiles, own slots in nearly every tile,
+    no softening, lists near and far."""
+    import paper_0902_4463_amd as g6
+    jm = workloads.random_cluster(n, seed=4200 + n)
+    ni = min(ni, n)
+    slots = workloads.active_set(n, ni, seed=ni)
+    ntiles = (n + 255) // 256
+    ipw = 32
+    while ipw < min(ni, 256):
+        ipw *= 2
+    with g6.Session(4, precision=prec) as s:
+        s.load(jm)
+        xi, vi = jm.x[slots], jm.v[slots]
+        a = evaluate(g6, s, jm, slots, xi, vi, 0.0, 0.02, (0, 0))
+        got = g6.g6mi_get_shape(s.id)
+        # one tile per piece; the last split's pieces may be empty
+        assert got["i_per_group"] == ipw and ntiles <= got["j_splits"] < ntiles + max(1, ntiles // 8)
+        b = evaluate(g6, s, jm, slots, xi, vi, 0.0, 0.02, (ipw, max(1, ntiles // 8)))
+    assert_same_sums(a, b)
