@@ -78,6 +78,47 @@ hipError_t ensure(PinBuf &b, size_t bytes) {
   return e;
 }
 
+// Particle index -> j-slot.  Small non-negative indices (the usual case:
+// indices about as many as slots) are looked up in an array, the rest in a
+// hash table; a lookup per i-particle and an insertion per stored particle
+// is most of what a small GRAPE call does on the host.
+class SlotMap {
+  std::vector<int> dense_;
+  std::unordered_map<int, int> rest_;
+
+public:
+  // the slot of index, or -1
+  int find(int index) const {
+    if (index >= 0 && static_cast<size_t>(index) < dense_.size()) return dense_[index];
+    if (rest_.empty()) return -1;
+    const auto it = rest_.find(index);
+    return it == rest_.end() ? -1 : it->second;
+  }
+  // nslots: slots of the j-memory so far, which bounds the array
+  void set(int index, int slot, size_t nslots) {
+    const size_t limit = std::max<size_t>(size_t(1) << 16, 8 * nslots);
+    if (index >= 0 && static_cast<size_t>(index) >= dense_.size() && static_cast<size_t>(index) < limit) {
+      size_t n = std::max<size_t>(1024, dense_.size());
+      while (n <= static_cast<size_t>(index)) n *= 2;
+      dense_.resize(n, -1);
+      for (auto it = rest_.begin(); it != rest_.end();) {
+        if (it->first >= 0 && static_cast<size_t>(it->first) < n) {
+          dense_[it->first] = it->second;
+          it = rest_.erase(it);
+        } else {
+          ++it;
+        }
+      }
+    }
+    if (index >= 0 && static_cast<size_t>(index) < dense_.size()) dense_[index] = slot;
+    else rest_[index] = slot;
+  }
+  void erase(int index) {
+    if (index >= 0 && static_cast<size_t>(index) < dense_.size()) dense_[index] = -1;
+    else rest_.erase(index);
+  }
+};
+
 struct Handle {
   bool open = false;
   int device = 0;
@@ -98,7 +139,7 @@ struct Handle {
   std::vector<unsigned char> h_set, h_dirty;
   std::vector<int> dirty;
   size_t n_contig = 0; // slots 0..n_contig-1 have all been set
-  std::unordered_map<int, int> slot_of;
+  SlotMap slot_of;
   double ti = 0.0;
 
   // device j-memory
@@ -106,11 +147,12 @@ struct Handle {
   DevBuf d_jm, d_pred, d_stage;
   PinBuf h_stage;
   hipEvent_t stage_ev = nullptr;
-  bool stage_busy = false;
+  bool stage_busy = false;    // stage_ev tells when h_stage may be written again
+  bool stage_on_stream = false; // ... the handle's stream does (small host calls)
 
   // host-path i-block and outputs
   DevBuf d_i, d_out;
-  PinBuf h_i, h_out;
+  PinBuf h_i, h_out, h_nb;
 
   // work buffers
   DevBuf d_part, d_min, d_nnslot, d_nbcount, d_nblist, d_flags, d_ovf;
@@ -272,21 +314,24 @@ int ensure_jmem(Handle &h, size_t need) {
   return 0;
 }
 
-// Upload the staged j-records on stream s: pack them into pinned memory, one
-// H2D copy, then a scatter kernel into the structure-of-arrays master.
-int upload_dirty(Handle &h, hipStream_t s) {
-  if (h.dirty.empty()) return 0;
+// Wait until the pinned staging buffer may be written again.
+int wait_stage(Handle &h) {
+  if (h.stage_busy) HIPCHK(&h, hipEventSynchronize(h.stage_ev));
+  h.stage_busy = false;
+  if (h.stage_on_stream) HIPCHK(&h, hipStreamSynchronize(h.stream));
+  h.stage_on_stream = false;
+  return 0;
+}
+
+// Bytes of the staged records of nd slots, their slots after them.
+size_t stage_bytes(size_t nd) { return nd * (kRecDoubles * sizeof(double) + sizeof(int)); }
+
+// Pack the staged j-records into pinned memory (the buffer large enough and
+// free): the records, then their slots.
+void pack_dirty(Handle &h) {
   const size_t nd = h.dirty.size();
-  if (h.stage_busy) {
-    HIPCHK(&h, hipEventSynchronize(h.stage_ev));
-    h.stage_busy = false;
-  }
-  const size_t rec_bytes = nd * kRecDoubles * sizeof(double);
-  const size_t bytes = rec_bytes + nd * sizeof(int);
-  HIPCHK(&h, ensure(h.h_stage, bytes));
-  HIPCHK(&h, ensure(h.d_stage, bytes));
   double *rec = static_cast<double *>(h.h_stage.p);
-  int *slots = reinterpret_cast<int *>(static_cast<char *>(h.h_stage.p) + rec_bytes);
+  int *slots = reinterpret_cast<int *>(rec + nd * kRecDoubles);
   for (size_t q = 0; q < nd; ++q) {
     const int k = h.dirty[q];
     std::memcpy(rec + q * kRecDoubles, &h.h_rec[static_cast<size_t>(k) * kRecDoubles],
@@ -295,6 +340,18 @@ int upload_dirty(Handle &h, hipStream_t s) {
     h.h_dirty[k] = 0;
   }
   h.dirty.clear();
+}
+
+// Upload the staged j-records on stream s: pack them into pinned memory, one
+// H2D copy, then a scatter kernel into the structure-of-arrays master.
+int upload_dirty(Handle &h, hipStream_t s) {
+  if (h.dirty.empty()) return 0;
+  const size_t nd = h.dirty.size(), rec_bytes = nd * kRecDoubles * sizeof(double), bytes = stage_bytes(nd);
+  int rc = wait_stage(h);
+  if (rc) return rc;
+  HIPCHK(&h, ensure(h.h_stage, bytes));
+  HIPCHK(&h, ensure(h.d_stage, bytes));
+  pack_dirty(h);
   HIPCHK(&h, hipMemcpyAsync(h.d_stage.p, h.h_stage.p, bytes, hipMemcpyHostToDevice, s));
   const double *drec = static_cast<const double *>(h.d_stage.p);
   const int *dslots = reinterpret_cast<const int *>(static_cast<char *>(h.d_stage.p) + rec_bytes);
@@ -448,7 +505,7 @@ void choose_shape(Handle &h, int ni, int nj, int &ipw, int &nsplit, bool &one, b
 // (!free_splits) and whose nsplit splits over nib i-blocks make fewer than
 // two workgroups per compute unit, or 0: pieces as short as four workgroups
 // per compute unit allow.  Measured: 341 i-particles against 2^15 in
-// double-single 258 us of kernels in 16 splits of eight tiles, 52 us in 128
+// double-single 258 us of kernels in 16 splits of eight tiles, 57 us in 128
 // pieces of one; with two workgroups per compute unit (100 against 2^20)
 // the minima cost as much as the pieces gain.
 int piece_tiles(const Handle &h, int ipw, bool one, bool spatial, int ni, int nj, int nsplit) {
@@ -734,17 +791,25 @@ struct IBlockLayout {
   }
 };
 struct OutLayout {
-  size_t acc, jerk, pot, r2nn, nnb, flags, bytes;
+  size_t acc, jerk, pot, r2nn, nnb, bytes;
   explicit OutLayout(size_t n) {
     acc = 0;
     jerk = acc + 3 * n * sizeof(double);
     pot = jerk + 3 * n * sizeof(double);
     r2nn = pot + n * sizeof(double);
     nnb = r2nn + n * sizeof(double);
-    flags = round_up(nnb + n * sizeof(int), 16);
-    bytes = flags + 16;
+    bytes = nnb + n * sizeof(int);
   }
 };
+
+// Host calls up to these sizes exchange their data without the copy engine:
+// one kernel reads the staged j-records and the i-block from pinned host
+// memory (at most kPinnedIn bytes) and the reduction writes the results of at
+// most kPinnedOutNi i-particles to it.  A copy costs 4 to 8 us of latency
+// whatever its size, and a call had four and the scatter: a step of 341
+// against 2^15 (as many records stored) takes 94 us so, 158 us with copies.
+constexpr size_t kPinnedIn = size_t(256) << 10;
+constexpr int kPinnedOutNi = 1024;
 
 int firsthalf_impl(Handle &h, int nj, int ni, const int *index, const double (*xi)[3],
                    const double (*vi)[3], double eps2, const double *h2) {
@@ -761,14 +826,14 @@ int firsthalf_impl(Handle &h, int nj, int ni, const int *index, const double (*x
   const size_t n = static_cast<size_t>(std::max(ni, 1));
   IBlockLayout il(n);
   OutLayout ol(n);
-  if (h.stage_busy) { // the i-block shares nothing with the j staging, but
-    HIPCHK(&h, hipEventSynchronize(h.stage_ev)); // keep one staging fence
-    h.stage_busy = false;
-  }
-  HIPCHK(&h, ensure(h.h_i, il.bytes));
-  HIPCHK(&h, ensure(h.d_i, il.bytes));
+  const size_t nd = h.dirty.size(), ibytes = round_up(il.bytes, 16);
+  const bool pinned_in = ibytes + stage_bytes(nd) <= kPinnedIn, pinned_out = ni <= kPinnedOutNi;
+  rc = wait_stage(h);
+  if (rc) return rc;
+  HIPCHK(&h, ensure(h.h_i, ibytes));
+  HIPCHK(&h, ensure(h.d_i, ibytes));
   HIPCHK(&h, ensure(h.h_out, ol.bytes));
-  HIPCHK(&h, ensure(h.d_out, ol.bytes));
+  if (!pinned_out) HIPCHK(&h, ensure(h.d_out, ol.bytes));
   char *hi = static_cast<char *>(h.h_i.p);
   double *pxi = reinterpret_cast<double *>(hi + il.xi);
   double *pvi = reinterpret_cast<double *>(hi + il.vi);
@@ -780,13 +845,21 @@ int firsthalf_impl(Handle &h, int nj, int ni, const int *index, const double (*x
       pvi[3 * i + d] = vi[i][d];
     }
     ph2[i] = h2 ? h2[i] : 0.0;
-    auto it = h.slot_of.find(index[i]);
-    pis[i] = (it != h.slot_of.end() && it->second < nj) ? it->second : -1;
+    const int slot = h.slot_of.find(index[i]);
+    pis[i] = slot < nj ? slot : -1;
   }
   hipStream_t s = h.stream;
-  HIPCHK(&h, hipMemcpyAsync(h.d_i.p, h.h_i.p, il.bytes, hipMemcpyHostToDevice, s));
+  if (pinned_in) {
+    HIPCHK(&h, ensure(h.h_stage, stage_bytes(nd)));
+    pack_dirty(h);
+    h.stage_on_stream = true;
+    HIPCHK(&h, launch_stage_in(static_cast<int>(nd), static_cast<const double *>(h.h_stage.p), h.jm, ibytes,
+                               h.h_i.p, h.d_i.p, s));
+  } else {
+    HIPCHK(&h, hipMemcpyAsync(h.d_i.p, h.h_i.p, il.bytes, hipMemcpyHostToDevice, s));
+  }
   char *di = static_cast<char *>(h.d_i.p);
-  char *dout = static_cast<char *>(h.d_out.p);
+  char *dout = static_cast<char *>(pinned_out ? h.h_out.p : h.d_out.p);
   rc = enqueue_calc(h, nj, ni, reinterpret_cast<const int *>(di + il.islot),
                     reinterpret_cast<const double *>(di + il.xi),
                     reinterpret_cast<const double *>(di + il.vi),
@@ -797,8 +870,7 @@ int firsthalf_impl(Handle &h, int nj, int ni, const int *index, const double (*x
                     reinterpret_cast<int *>(dout + ol.nnb),
                     reinterpret_cast<double *>(dout + ol.r2nn), s);
   if (rc) return rc;
-  HIPCHK(&h, hipMemcpyAsync(dout + ol.flags, h.c_flags, sizeof(int), hipMemcpyDeviceToDevice, s));
-  HIPCHK(&h, hipMemcpyAsync(h.h_out.p, h.d_out.p, ol.bytes, hipMemcpyDeviceToHost, s));
+  if (!pinned_out) HIPCHK(&h, hipMemcpyAsync(h.h_out.p, h.d_out.p, ol.bytes, hipMemcpyDeviceToHost, s));
   h.c_index.assign(index, index + ni);
   return 0;
 }
@@ -815,6 +887,7 @@ int lasthalf_impl(int id, int nj, int ni, const int *index, double eps2, double 
   }
   HIPCHK(h, hipSetDevice(h->device));
   HIPCHK(h, hipStreamSynchronize(h->stream));
+  h->stage_on_stream = false;
   if (nj != h->c_nj || ni != h->c_ni || eps2 != h->c_eps2 ||
       (ni > 0 && (!index || std::memcmp(index, h->c_index.data(), sizeof(int) * ni) != 0)))
     return fail(h, G6MI_EINVAL, "lasthalf arguments differ from firsthalf");
@@ -827,19 +900,20 @@ int lasthalf_impl(int id, int nj, int ni, const int *index, double eps2, double 
   const double *pp = reinterpret_cast<const double *>(ho + ol.pot);
   const double *pr = reinterpret_cast<const double *>(ho + ol.r2nn);
   const int *pn = reinterpret_cast<const int *>(ho + ol.nnb);
-  const int flags = *reinterpret_cast<const int *>(ho + ol.flags);
+  bool finite = true;
   for (int i = 0; i < ni; ++i) {
     for (int d = 0; d < 3; ++d) {
       acc[i][d] = pa[3 * i + d];
       jerk[i][d] = pj[3 * i + d];
     }
     pot[i] = pp[i];
+    finite = finite && finite3(pa + 3 * i) && finite3(pj + 3 * i) && std::isfinite(pp[i]);
     if (nnbindex) nnbindex[i] = pn[i];
   }
   h->r_nnb.assign(pn, pn + ni);
   h->r_r2nn.assign(pr, pr + ni);
   h->res_valid = true;
-  return (ni > 0 && (flags & 1)) ? G6MI_WARN : G6MI_OK;
+  return finite ? G6MI_OK : G6MI_WARN;
 }
 
 // ------------------------------------------------------------ batched path
@@ -1135,7 +1209,7 @@ G6MI_API int g6_close(int id) {
                     &h->d_min, &h->d_nnslot, &h->d_nbcount, &h->d_nblist, &h->d_flags,
                     &h->d_ovf, &h->d_cl, &h->d_plan, &h->d_items, &h->d_bwork, &h->d_ibcl, &h->d_sp})
     b->release();
-  for (PinBuf *b : {&h->h_stage, &h->h_i, &h->h_out, &h->h_cl}) b->release();
+  for (PinBuf *b : {&h->h_stage, &h->h_i, &h->h_out, &h->h_nb, &h->h_cl}) b->release();
   if (h->cl_ev) (void)hipEventDestroy(h->cl_ev);
   for (auto &q : h->evs)
     for (auto &ev : q) (void)hipEventDestroy(ev);
@@ -1184,12 +1258,9 @@ void store_j(Handle *h, int address, int index, double tj, double mass, const do
   r[14] = static_cast<double>(index);
   r[15] = 0.0;
   const int old = h->h_index[address];
-  if (old != index) {
-    auto it = h->slot_of.find(old);
-    if (old >= 0 && it != h->slot_of.end() && it->second == address) h->slot_of.erase(it);
-  }
+  if (old != index && old >= 0 && h->slot_of.find(old) == address) h->slot_of.erase(old);
   h->h_index[address] = index;
-  h->slot_of[index] = address;
+  h->slot_of.set(index, address, h->h_index.size());
   h->h_set[address] = 1;
   while (h->n_contig < h->h_set.size() && h->h_set[h->n_contig]) ++h->n_contig;
   mark_dirty(*h, address);
@@ -1293,12 +1364,31 @@ G6MI_API int g6_read_neighbour_list(int id) {
   HIPCHK(h, hipSetDevice(h->device));
   HIPCHK(h, hipStreamSynchronize(h->c_stream));
   const size_t n = static_cast<size_t>(h->c_ni);
-  if (n > 0 && h->c_nbl) {
+  const ForceArgs &ca = h->c_batch ? h->c_bargs.fa : h->c_args;
+  const int *d_status = h->c_batch ? h->c_bargs.status : h->c_flags;
+  // few lists: one kernel writes status words, counts and the stored entries
+  // to pinned host memory
+  const bool small = n > 0 && n <= static_cast<size_t>(kPinnedOutNi);
+  const int *out = nullptr;
+  int status[kStatusWords] = {0, 0};
+  auto fetch = [&]() -> int {
+    if (small) {
+      HIPCHK(h, ensure(h->h_nb, (kStatusWords + n + n * kNbMax) * sizeof(int)));
+      out = static_cast<const int *>(h->h_nb.p);
+      HIPCHK(h, launch_export_lists(static_cast<int>(n), d_status, ca.nb_count, ca.nb_slot,
+                                    static_cast<int *>(h->h_nb.p), h->c_stream));
+      HIPCHK(h, hipStreamSynchronize(h->c_stream));
+      std::memcpy(status, out, sizeof(status));
+    } else {
+      HIPCHK(h, hipMemcpy(status, d_status, sizeof(status), hipMemcpyDeviceToHost));
+    }
+    return 0;
+  };
+  if (n > 0) {
+    int rc = fetch();
+    if (rc) return rc;
     // overflowed lists: keep the G6MI_NB_MAX smallest indices (exact pass)
-    int status[kStatusWords] = {0, 0};
-    HIPCHK(h, hipMemcpy(status, h->c_batch ? h->c_bargs.status : h->c_flags, sizeof(status),
-                        hipMemcpyDeviceToHost));
-    if (status[kStatusOverflowCount] > 0 && !h->nb_exact_done) {
+    if (h->c_nbl && status[kStatusOverflowCount] > 0 && !h->nb_exact_done) {
       if (h->c_batch)
         HIPCHK(h, launch_batch_nb_exact(h->c_prec, h->c_bargs, status[kStatusOverflowCount], h->c_stream));
       else if (h->c_fused)
@@ -1309,12 +1399,19 @@ G6MI_API int g6_read_neighbour_list(int id) {
                                   status[kStatusOverflowCount], h->c_stream));
       HIPCHK(h, hipStreamSynchronize(h->c_stream));
       h->nb_exact_done = true;
+      if (small) rc = fetch();
+      if (rc) return rc;
     }
   }
-  h->r_nbcount.assign(n, 0);
-  h->r_nblist.assign(n * kNbMax, -1);
-  if (n > 0) {
-    const ForceArgs &ca = h->c_batch ? h->c_bargs.fa : h->c_args;
+  h->r_nbcount.resize(n);
+  h->r_nblist.resize(n * kNbMax);
+  if (small) {
+    const int *cnt = out + kStatusWords, *lists = cnt + n;
+    std::memcpy(h->r_nbcount.data(), cnt, n * sizeof(int));
+    for (size_t i = 0; i < n; ++i)
+      std::memcpy(&h->r_nblist[i * kNbMax], lists + i * kNbMax,
+                  sizeof(int) * static_cast<size_t>(std::max(0, std::min(cnt[i], kNbMax))));
+  } else if (n > 0) {
     HIPCHK(h, hipMemcpy(h->r_nbcount.data(), ca.nb_count, n * sizeof(int), hipMemcpyDeviceToHost));
     HIPCHK(h, hipMemcpy(h->r_nblist.data(), ca.nb_slot, n * kNbMax * sizeof(int), hipMemcpyDeviceToHost));
   }
@@ -1514,13 +1611,12 @@ G6MI_API int g6mi_set_j_particles_device(int id, int nj, const double *d_t, cons
   }
   for (int k = 0; k < nj; ++k) {
     const int old = h->h_index[k];
-    auto it = h->slot_of.find(old);
-    if (old >= 0 && it != h->slot_of.end() && it->second == k) h->slot_of.erase(it);
+    if (old >= 0 && h->slot_of.find(old) == k) h->slot_of.erase(old);
   }
   for (int k = 0; k < nj; ++k) {
     h->h_rec[static_cast<size_t>(k) * kRecDoubles + 14] = static_cast<double>(idx[k]);
     h->h_index[k] = idx[k];
-    h->slot_of[idx[k]] = k;
+    h->slot_of.set(idx[k], k, h->h_index.size());
     h->h_set[k] = 1;
   }
   while (h->n_contig < h->h_set.size() && h->h_set[h->n_contig]) ++h->n_contig;

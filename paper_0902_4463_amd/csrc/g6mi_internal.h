@@ -158,6 +158,16 @@ hipError_t launch_nb_exact_fused(int prec, const ForceArgs &a, const JMem &jm, d
 hipError_t launch_scatter(int nd, const int *slots, const double *rec,
                           const JMem &jm, hipStream_t s);
 
+// The same straight from pinned host memory (rec, then the slots), with the
+// ibytes (a multiple of 16) of an i-block copied from i_src (pinned) to i_dst.
+hipError_t launch_stage_in(int nd, const double *rec, const JMem &jm, size_t ibytes, const void *i_src,
+                           void *i_dst, hipStream_t s);
+
+// Neighbour lists of n rows to pinned host memory: out = status words, counts
+// [n], lists [n][kNbMax] of which the stored entries are written.
+hipError_t launch_export_lists(int n, const int *status, const int *nb_count, const int *nb_slot, int *out,
+                               hipStream_t s);
+
 // Copy nj records given as device arrays (row-major [nj][3] vectors) into
 // slots 0..nj-1 of the j-memory.
 hipError_t launch_load(int nj, const double *t, const double *m,

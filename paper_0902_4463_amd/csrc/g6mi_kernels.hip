@@ -527,23 +527,57 @@ __global__ __launch_bounds__(kWG) void nb_exact_fused_kernel(ForceArgs a, JMem j
 
 // ------------------------------------------------------------ j-memory I/O
 
-__global__ __launch_bounds__(256) void scatter_kernel(int nd, const int *__restrict__ slots,
-                                                      const double *__restrict__ rec, JMem jm) {
-  const int q = blockIdx.x * 256 + threadIdx.x;
+// Component c of a staged record (kRecDoubles = 16 doubles: t, m, x, v, a2,
+// j6, index, pad) to slot k of the j-memory.
+__device__ __forceinline__ void scatter_component(const JMem &jm, size_t k, int c, double v) {
+  if (c == 0) jm.t[k] = v;
+  else if (c == 1) jm.m[k] = v;
+  else if (c < 5) jm.x[(c - 2) * jm.cap + k] = v;
+  else if (c < 8) jm.v[(c - 5) * jm.cap + k] = v;
+  else if (c < 11) jm.a2[(c - 8) * jm.cap + k] = v;
+  else if (c < 14) jm.j6[(c - 11) * jm.cap + k] = v;
+  else if (c == 14) jm.index[k] = static_cast<int>(v);
+}
+
+// Sixteen lanes per record, so that a record is one contiguous read: bound
+// by the latency of that read and the scattered stores.
+__device__ __forceinline__ void scatter_records(int block, int nd, const int *__restrict__ slots,
+                                                const double *__restrict__ rec, const JMem &jm) {
+  const int q = block * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
   if (q >= nd) return;
   const size_t k = static_cast<size_t>(slots[q]);
-  if (k >= jm.cap) return;
-  const double *r = rec + 16 * static_cast<size_t>(q);
-  jm.t[k] = r[0];
-  jm.m[k] = r[1];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    jm.x[d * jm.cap + k] = r[2 + d];
-    jm.v[d * jm.cap + k] = r[5 + d];
-    jm.a2[d * jm.cap + k] = r[8 + d];
-    jm.j6[d * jm.cap + k] = r[11 + d];
+  if (k < jm.cap) scatter_component(jm, k, c, rec[16 * static_cast<size_t>(q) + c]);
+}
+
+__global__ __launch_bounds__(256) void scatter_kernel(int nd, const int *__restrict__ slots,
+                                                      const double *__restrict__ rec, JMem jm) {
+  scatter_records(blockIdx.x, nd, slots, rec, jm);
+}
+
+// Inputs of a small host call from pinned host memory: the first workgroups
+// scatter the nd staged records (their slots follow them), the others copy
+// the i-block.
+__global__ __launch_bounds__(256) void stage_in_kernel(int nd, const double *__restrict__ rec, JMem jm,
+                                                       int rec_blocks, int n16, const double2 *__restrict__ src,
+                                                       double2 *__restrict__ dst) {
+  if (static_cast<int>(blockIdx.x) < rec_blocks) {
+    scatter_records(blockIdx.x, nd, reinterpret_cast<const int *>(rec + 16 * static_cast<size_t>(nd)), rec, jm);
+    return;
   }
-  jm.index[k] = static_cast<int>(r[14]);
+  const int k = (static_cast<int>(blockIdx.x) - rec_blocks) * 256 + threadIdx.x;
+  if (k < n16) dst[k] = src[k];
+}
+
+// One wave per row (see launch_export_lists).
+__global__ __launch_bounds__(64) void export_lists_kernel(int n, const int *__restrict__ status,
+                                                          const int *__restrict__ nb_count,
+                                                          const int *__restrict__ nb_slot, int *__restrict__ out) {
+  const int i = blockIdx.x, lane = threadIdx.x;
+  if (i == 0 && lane < kStatusWords) out[lane] = status[lane];
+  const int cnt = nb_count[i];
+  if (lane == 0) out[kStatusWords + i] = cnt;
+  int *lst = out + kStatusWords + n + static_cast<size_t>(i) * kNbMax;
+  for (int k = lane; k < min(cnt, kNbMax); k += 64) lst[k] = nb_slot[static_cast<size_t>(i) * kNbMax + k];
 }
 
 __global__ __launch_bounds__(256) void load_kernel(int nj, const double *__restrict__ t,
@@ -767,7 +801,24 @@ hipError_t launch_nb_exact_fused(int prec, const ForceArgs &a, const JMem &jm, d
 hipError_t launch_scatter(int nd, const int *slots, const double *rec, const JMem &jm,
                           hipStream_t s) {
   if (nd <= 0) return hipSuccess;
-  hipLaunchKernelGGL(scatter_kernel, dim3(blocks_for(nd)), dim3(256), 0, s, nd, slots, rec, jm);
+  hipLaunchKernelGGL(scatter_kernel, dim3(blocks_for(16L * nd)), dim3(256), 0, s, nd, slots, rec, jm);
+  return hipGetLastError();
+}
+
+hipError_t launch_stage_in(int nd, const double *rec, const JMem &jm, size_t ibytes, const void *i_src,
+                           void *i_dst, hipStream_t s) {
+  const int rec_blocks = static_cast<int>(blocks_for(16L * nd)), n16 = static_cast<int>(ibytes / 16);
+  hipLaunchKernelGGL(stage_in_kernel, dim3(static_cast<unsigned>(rec_blocks) + blocks_for(n16)), dim3(256), 0, s,
+                     nd, rec, jm, rec_blocks, n16, static_cast<const double2 *>(i_src),
+                     static_cast<double2 *>(i_dst));
+  return hipGetLastError();
+}
+
+hipError_t launch_export_lists(int n, const int *status, const int *nb_count, const int *nb_slot, int *out,
+                               hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(export_lists_kernel, dim3(static_cast<unsigned>(n)), dim3(64), 0, s, n, status, nb_count,
+                     nb_slot, out);
   return hipGetLastError();
 }
 

@@ -90,3 +90,42 @@ def test_pieces_match_whole_splits(prec, ni, n):
         assert got["i_per_group"] == ipw and ntiles <= got["j_splits"] < ntiles + max(1, ntiles // 8)
         b = evaluate(g6, s, jm, slots, xi, vi, 0.0, 0.02, (ipw, max(1, ntiles // 8)))
     assert_same_sums(a, b)
+
+
+@pytest.mark.parametrize("ni,changed", [(1, 1), (17, 0), (341, 341), (1024, 700), (1025, 3), (1500, 2500)])
+def test_host_calls_with_and_without_copies(ni, changed):
+    """Host calls whose inputs and results travel through pinned memory
+    without copies (small blocks, few stored records) and those that use
+    copies, against the device-resident path on the same particles; a second
+    call stores `changed` records first.  Negative and large particle indices
+    look their slots up outside the index array."""
+    import torch
+
+    import paper_0902_4463_amd as g6
+    n = 3000
+    jm = workloads.random_cluster(n, seed=4300)
+    jm.index[:] = np.arange(n) * 3 - 100
+    jm.index[7::11] = np.arange(len(jm.index[7::11])) + 10 ** 8
+    slots = workloads.active_set(n, ni, seed=ni)
+    new = np.arange(n)[::-1][:changed]
+    xi, vi = jm.x[slots], jm.v[slots]
+    dev = [torch.from_numpy(np.ascontiguousarray(q)).cuda() for q in (slots.astype(np.int32), xi, vi, np.full(ni, 4e-4))]
+    with g6.Session(4) as s:
+        s.load(jm)
+        for call in range(2):
+            host = s.calc(n, jm.meta["ti"], jm.index[slots], xi, vi, 1e-6, 4e-4)
+            acc, jerk = (torch.zeros(ni, 3, device="cuda", dtype=torch.float64) for _ in range(2))
+            pot = torch.zeros(ni, device="cuda", dtype=torch.float64)
+            nnb = torch.zeros(ni, device="cuda", dtype=torch.int32)
+            torch.cuda.synchronize()
+            g6.check(s.id, g6.g6mi_calc_device(s.id, n, ni, dev[0], dev[1], dev[2], 1e-6, dev[3], acc, jerk, pot, nnb))
+            assert g6.g6mi_last_status(s.id) == 0
+            torch.cuda.synchronize()
+            assert np.array_equal(host["acc"], acc.cpu().numpy()) and np.array_equal(host["jerk"], jerk.cpu().numpy())
+            assert np.array_equal(host["pot"], pot.cpu().numpy()) and np.array_equal(host["nn_index"], nnb.cpu().numpy())
+            assert not np.any(host["nn_index"] == jm.index[slots])
+            if call == 0 and changed:
+                jm.x[new] += 0.01
+                jm.index[new] += 5 * 10 ** 8
+                g6.check(s.id, g6.g6mi_set_j_particles(s.id, changed, new, jm.index[new], jm.t[new], None, jm.m[new],
+                                                       jm.j6[new], jm.a2[new], jm.v[new], jm.x[new]))
