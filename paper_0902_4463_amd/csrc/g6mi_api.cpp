@@ -214,9 +214,8 @@ struct Handle {
     double *jm_t = nullptr; // the j-memory the state lives in
     size_t cap = 0;
     DevBuf d_ctl, d_state, d_block;
-    PinBuf h_ctl;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    PinBuf h_ctl, h_rows;
+    hipGraphExec_t exec[3] = {nullptr, nullptr, nullptr}; // graphs of kHsGraphSteps[] block steps
     std::vector<uint64_t> key;
   } hs;
 };
@@ -1201,10 +1200,11 @@ G6MI_API int g6_close(int id) {
   (void)hipStreamSynchronize(h->stream);
   if (h->c_stream && h->c_stream != h->stream) (void)hipStreamSynchronize(h->c_stream);
   destroy_graph(*h);
-  if (h->hs.exec) (void)hipGraphExecDestroy(h->hs.exec);
-  if (h->hs.graph) (void)hipGraphDestroy(h->hs.graph);
+  for (hipGraphExec_t e : h->hs.exec)
+    if (e) (void)hipGraphExecDestroy(e);
   for (DevBuf *b : {&h->hs.d_ctl, &h->hs.d_state, &h->hs.d_block}) b->release();
   h->hs.h_ctl.release();
+  h->hs.h_rows.release();
   for (DevBuf *b : {&h->d_jm, &h->d_pred, &h->d_stage, &h->d_i, &h->d_out, &h->d_part,
                     &h->d_min, &h->d_nnslot, &h->d_nbcount, &h->d_nblist, &h->d_flags,
                     &h->d_ovf, &h->d_cl, &h->d_plan, &h->d_items, &h->d_bwork, &h->d_ibcl, &h->d_sp})
@@ -1898,12 +1898,40 @@ G6MI_API int g6mi_batch_autotune(int id, int ncl, const g6mi_cluster *cl, int ni
 // ------------------------------------------------ device-resident block steps
 
 namespace {
+// Block steps per replayed graph, as many as are left: the gap between two
+// graphs is several us, more than the gaps between the three kernels of a step
+// inside one (an interval of 290 steps of 32768 particles took 12.3 ms with
+// graphs of one step, 11.2 ms of eight, 11.1 ms of 16 and of 32).
+constexpr int kHsGraphSteps[] = {16, 4, 1};
+constexpr int kHsGraphs = 3;
+
 void hs_destroy_graph(Handle &h) {
-  if (h.hs.exec) (void)hipGraphExecDestroy(h.hs.exec);
-  if (h.hs.graph) (void)hipGraphDestroy(h.hs.graph);
-  h.hs.exec = nullptr;
-  h.hs.graph = nullptr;
+  for (hipGraphExec_t &e : h.hs.exec) {
+    if (e) (void)hipGraphExecDestroy(e);
+    e = nullptr;
+  }
   h.hs.key.clear();
+}
+
+// A graph of `steps` block steps.
+int hs_capture(Handle &h, const BatchArgs &b, int steps, hipStream_t s, hipGraphExec_t *exec) {
+  const HermiteArgs &a = h.hs.a;
+  HIPCHK(&h, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+  hipError_t e = hipSuccess;
+  for (int k = 0; k < steps && e == hipSuccess; ++k) {
+    e = launch_hs_force(h.prec, a, b, b.grid, s);
+    if (e == hipSuccess) e = launch_hs_correct(a, b, b.grid, s);
+  }
+  hipGraph_t g = nullptr;
+  const hipError_t ec = hipStreamEndCapture(s, &g);
+  if (e == hipSuccess) e = ec;
+  if (e == hipSuccess) {
+    e = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
+    if (e != hipSuccess) *exec = nullptr;
+  }
+  if (g) (void)hipGraphDestroy(g);
+  if (e != hipSuccess) return hip_fail(&h, e, "block-step graph");
+  return 0;
 }
 
 // Batch arguments of the current block (descriptor in the control block).
@@ -2001,7 +2029,7 @@ G6MI_API int g6mi_hermite_init(int id, int n, double eps2, double h2, double eta
   rc = hs_batch(*h, b);
   if (rc) return rc;
   HIPCHK(h, launch_hs_reset(a, s));
-  HIPCHK(h, launch_hs_select(a, b, s));
+  HIPCHK(h, launch_hs_first(a, b, s));
   HIPCHK(h, launch_batch_force(h->prec, b, b.grid, s));
   HIPCHK(h, launch_hs_start(a, s));
   rc = hs_read_ctl(*h, s, c);
@@ -2032,41 +2060,35 @@ G6MI_API int g6mi_hermite_advance(int id, double t_end, long long max_steps, dou
   BatchArgs b;
   rc = hs_batch(*h, b);
   if (rc) return rc;
-  const int grid = b.grid;
-  std::vector<uint64_t> key = graph_key(*h, b, grid, s);
-  if (!hs.exec || key != hs.key) {
+  std::vector<uint64_t> key = graph_key(*h, b, b.grid, s);
+  if (key != hs.key) {
     hs_destroy_graph(*h);
-    HIPCHK(h, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    hipError_t e = launch_hs_select(a, b, s);
-    if (e == hipSuccess) e = launch_batch_items(h->prec, b, grid, s);
-    if (e == hipSuccess) e = launch_hs_correct(a, b, grid, s);
-    hipGraph_t g = nullptr;
-    const hipError_t ec = hipStreamEndCapture(s, &g);
-    if (e == hipSuccess) e = ec;
-    if (e != hipSuccess) {
-      if (g) (void)hipGraphDestroy(g);
-      return hip_fail(h, e, "block-step graph capture");
-    }
-    hs.graph = g;
-    e = hipGraphInstantiate(&hs.exec, g, nullptr, nullptr, 0);
-    if (e != hipSuccess) {
-      hs.exec = nullptr;
+    for (int g = 0; g < kHsGraphs && !rc; ++g) rc = hs_capture(*h, b, kHsGraphSteps[g], s, &hs.exec[g]);
+    if (rc) {
       hs_destroy_graph(*h);
-      return hip_fail(h, e, "hipGraphInstantiate");
+      return rc;
     }
     hs.key = std::move(key);
   }
   // Replays past the last block before t_end select nothing and change
-  // nothing, so steps are launched in chunks between checks.
-  long long launched = 0;
+  // nothing, so steps are launched in chunks between checks: as many as the
+  // last chunk's pace leaves up to t_end, at most 32.
+  long long launched = 0, chunk = 32;
+  double since = NAN; // time before the last chunk
   bool done = false;
   while (launched < max_steps && !done) {
-    const long long chunk = std::min<long long>(32, max_steps - launched);
-    for (long long q = 0; q < chunk; ++q) HIPCHK(h, hipGraphLaunch(hs.exec, s));
+    chunk = std::min(chunk, max_steps - launched);
+    long long left = chunk;
+    for (int g = 0; g < kHsGraphs; ++g)
+      for (; left >= kHsGraphSteps[g]; left -= kHsGraphSteps[g]) HIPCHK(h, hipGraphLaunch(hs.exec[g], s));
     launched += chunk;
     rc = hs_read_ctl(*h, s, c);
     if (rc) return rc;
     done = c.done != 0;
+    // a block step past t_end ends the run: one replay more than are left
+    const double pace = (c.time - since) / static_cast<double>(chunk), rest = (t_end - c.time) / pace;
+    chunk = rest >= 0.0 && rest < 31.0 ? static_cast<long long>(rest) + 1 : 32;
+    since = c.time;
   }
   if (launched == 0) {
     rc = hs_read_ctl(*h, s, c);
@@ -2093,45 +2115,36 @@ G6MI_API int g6mi_hermite_state(int id, int n, double x[][3], double v[][3], dou
   HIPCHK(h, hipSetDevice(h->device));
   HIPCHK(h, hipStreamSynchronize(h->stream));
   if (n == 0) return G6MI_OK;
-  const HermiteArgs &a = hs.a;
-  const size_t cap = hs.cap, nn = static_cast<size_t>(n);
-  std::vector<double> col(nn);
-  auto get = [&](const double *src) -> int {
-    HIPCHK(h, hipMemcpy(col.data(), src, nn * sizeof(double), hipMemcpyDeviceToHost));
-    return 0;
-  };
-  // vectors: component d of slot k at [d * cap + k]; also refresh the host
-  // master copy of the j-memory (x, v, a/2, jerk/6, t)
-  struct Vec {
-    const double *src;
-    double (*out)[3];
-    int rec;    // offset of the vector in the staged record
-    double div; // the record holds value / div (a/2, jerk/6)
-  } vecs[4] = {{a.jm.x, x, 2, 1.0}, {a.jm.v, v, 5, 1.0}, {a.acc, acc, 8, 2.0}, {a.jrk, jerk, 11, 6.0}};
-  for (const Vec &q : vecs)
-    for (int d = 0; d < 3; ++d) {
-      int rc = get(q.src + d * cap);
-      if (rc) return rc;
-      for (size_t k = 0; k < nn; ++k) {
-        if (q.out) q.out[k][d] = col[k];
-        h->h_rec[k * kRecDoubles + q.rec + d] = col[k] / q.div;
+  // rows of kHsRowDoubles doubles through pinned memory, kRows at a time; the
+  // host master copy of the j-memory (t, x, v, a/2, jerk/6) is refreshed too
+  constexpr int kRows = 1 << 16;
+  HIPCHK(h, ensure(hs.h_rows, static_cast<size_t>(std::min(n, kRows)) * kHsRowDoubles * sizeof(double)));
+  for (int k0 = 0; k0 < n; k0 += kRows) {
+    const int m = std::min(kRows, n - k0);
+    HIPCHK(h, launch_hs_export(hs.a, k0, m, static_cast<double *>(hs.h_rows.p), h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    const double *r = static_cast<const double *>(hs.h_rows.p);
+    for (int k = k0; k < k0 + m; ++k, r += kHsRowDoubles) {
+      double *rec = &h->h_rec[static_cast<size_t>(k) * kRecDoubles];
+      rec[0] = r[0];
+      for (int d = 0; d < 3; ++d) {
+        rec[2 + d] = r[1 + d];
+        rec[5 + d] = r[4 + d];
+        rec[8 + d] = r[7 + d] / 2.0;
+        rec[11 + d] = r[10 + d] / 6.0;
       }
+      auto vec = [&](double(*out)[3], int c) {
+        if (out)
+          for (int d = 0; d < 3; ++d) out[k][d] = r[c + d];
+      };
+      vec(x, 1);
+      vec(v, 4);
+      vec(acc, 7);
+      vec(jerk, 10);
+      if (t) t[k] = r[0];
+      if (pot) pot[k] = r[13];
+      if (dt) dt[k] = r[14];
     }
-  int rc = get(a.jm.t);
-  if (rc) return rc;
-  for (size_t k = 0; k < nn; ++k) {
-    if (t) t[k] = col[k];
-    h->h_rec[k * kRecDoubles] = col[k];
-  }
-  if (pot) {
-    rc = get(a.pot);
-    if (rc) return rc;
-    std::copy(col.begin(), col.end(), pot);
-  }
-  if (dt) {
-    rc = get(a.dt);
-    if (rc) return rc;
-    std::copy(col.begin(), col.end(), dt);
   }
   return G6MI_OK;
 }

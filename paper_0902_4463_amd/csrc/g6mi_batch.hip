@@ -386,7 +386,7 @@ static void launch_batch_prec(const BatchArgs &b, int grid, hipStream_t s) {
   }
 }
 
-hipError_t launch_batch_items(int prec, const BatchArgs &b, int grid, hipStream_t s) {
+static hipError_t launch_batch_items(int prec, const BatchArgs &b, int grid, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
   switch (prec) {
   case G6MI_PREC_FP32: launch_batch_prec<G6MI_PREC_FP32>(b, grid, s); break;

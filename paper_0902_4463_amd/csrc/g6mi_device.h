@@ -885,7 +885,8 @@ struct NarrowLane {
   // synchronises before reusing it), and lane il adds parts 1 .. P - 1 in
   // order.  Afterwards the lanes with sub == 0 (tid = il) hold the
   // i-particle's totals in t and its nearest-neighbour candidate in
-  // (bestd, bslot).
+  // (bestd, bslot); NN = false leaves the candidates out.
+  template <bool NN = true>
   __device__ __forceinline__ void lane_sum(double *red, int tid, int il, int ipw, double &bestd,
                                            int &bslot) {
     bestd = static_cast<double>(ebest);
@@ -898,9 +899,11 @@ struct NarrowLane {
         t.jrk[d] += __shfl_xor(t.jrk[d], m);
       }
       t.pot += __shfl_xor(t.pot, m);
-      const double r2o = __shfl_xor(bestd, m);
-      const int so = __shfl_xor(bslot, m);
-      nn_merge_lane(r2o, so, bestd, bslot);
+      if constexpr (NN) {
+        const double r2o = __shfl_xor(bestd, m);
+        const int so = __shfl_xor(bslot, m);
+        nn_merge_lane(r2o, so, bestd, bslot);
+      }
     }
     const int stride = ipw < 64 ? 64 : ipw; // lanes between the holders of two parts
     const int nparts = kWG / stride;
@@ -914,8 +917,10 @@ struct NarrowLane {
         red[(3 + d) * kWG + tid] = t.jrk[d];
       }
       red[6 * kWG + tid] = t.pot;
-      red[7 * kWG + tid] = bestd;
-      rslot[tid] = bslot;
+      if constexpr (NN) {
+        red[7 * kWG + tid] = bestd;
+        rslot[tid] = bslot;
+      }
     }
     __syncthreads();
     if (tid == il) {
@@ -927,7 +932,7 @@ struct NarrowLane {
           t.jrk[d] += red[(3 + d) * kWG + o];
         }
         t.pot += red[6 * kWG + o];
-        nn_merge_lane(red[7 * kWG + o], rslot[o], bestd, bslot);
+        if constexpr (NN) nn_merge_lane(red[7 * kWG + o], rslot[o], bestd, bslot);
       }
     }
   }

@@ -302,8 +302,6 @@ constexpr int kPlanZeroChunk = 4096;
 hipError_t launch_batch_plan(const BatchArgs &b, hipStream_t s);
 // the persistent kernel and the reduction
 hipError_t launch_batch_force(int prec, const BatchArgs &b, int grid, hipStream_t s);
-// the persistent kernel alone (its partials reduced by the caller's launch)
-hipError_t launch_batch_items(int prec, const BatchArgs &b, int grid, hipStream_t s);
 hipError_t launch_batch_nb_exact(int prec, const BatchArgs &b, int novf, hipStream_t s);
 
 // Status flag of the batched launch: a cluster descriptor was out of range
@@ -315,13 +313,15 @@ constexpr int kFlagBadCluster = 4;
 // Control block of the device-resident Hermite integrator (device memory).
 //
 // Block times as order keys (the minimum over the grid is one atomicMin):
-// key[phase] holds this step's block time t_b; key[phase ^ 1] gathers the
-// next one, the minimum of t + dt over the particles the selection leaves
-// alone and over the corrected ones.  The publish launch between the two
-// clears key[phase] and flips phase.
+// key[phase] holds this step's block time t_b; key[phase ^ 1] = key[gather]
+// gathers the next one, the minimum of t + dt over the particles the
+// selection leaves alone and over the corrected ones.  The corrector's launch
+// clears key[phase], which only the launches before it read, and turns phase
+// over (in the first force evaluation the publish launch does).
 struct HermiteCtl {
   unsigned long long key[2];
   int phase;
+  int gather;                   // phase ^ 1, for the corrector's launch, which changes phase
   int ni_count;                 // particles selected so far in this step
   int done;                     // 1: no particle is due at or before t_end
   int flags;                    // bit 0: a non-finite force
@@ -347,13 +347,20 @@ struct HermiteArgs {
 };
 
 hipError_t launch_hs_reset(const HermiteArgs &h, hipStream_t s);
-// the block due at the next block time, its descriptor and its one-cluster
-// batch plan in b (two launches)
-hipError_t launch_hs_select(const HermiteArgs &h, const BatchArgs &b, hipStream_t s);
+// state of slots k0 .. k0 + n - 1 as rows of kHsRowDoubles doubles in pinned
+// host memory: t, x, v, acc, jerk, pot, dt, pad
+constexpr int kHsRowDoubles = 16;
+hipError_t launch_hs_export(const HermiteArgs &h, int k0, int n, double *rows, hipStream_t s);
+// the first block (every particle): selection, then its descriptor, one-
+// cluster batch plan and work tables in b
+hipError_t launch_hs_first(const HermiteArgs &h, const BatchArgs &b, hipStream_t s);
+// the block due at the next block time and its forces as split partials (two
+// launches)
+hipError_t launch_hs_force(int prec, const HermiteArgs &h, const BatchArgs &b, int grid, hipStream_t s);
 // after the first force evaluation (a whole batched force launch): store a,
 // jerk and potential and pick the first steps
 hipError_t launch_hs_start(const HermiteArgs &h, hipStream_t s);
-// after launch_batch_items: the batch reduction, corrector and new steps in
+// after launch_hs_force: the batch reduction, corrector and new steps in
 // one launch of `grid` workgroups
 hipError_t launch_hs_correct(const HermiteArgs &h, const BatchArgs &b, int grid, hipStream_t s);
 
