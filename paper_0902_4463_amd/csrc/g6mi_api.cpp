@@ -517,6 +517,19 @@ int piece_tiles(const Handle &h, int ipw, bool one, bool spatial, int ni, int nj
   return static_cast<int>(std::min(per, vper));
 }
 
+// Sets of lanes per workgroup of a calculation in nwg workgroups of pieces:
+// with one workgroup per compute unit or fewer, the latency of a lane's chain
+// is exposed and four sets share it, with two workgroups two sets; with more,
+// the compute unit's other workgroups cover it and the exchange of the group
+// sums only costs.  Measured (us per call; double-single unless said): 341
+// against 32768 (256 workgroups) 41 with four sets, 61 with one; 200 against
+// 50000 in float32 (196) 37 and 54; 100 against 100000 (391) 50 with four, 43
+// with two, 46 with one; 400 against 100000 (782) 123 with four, 106 with one.
+int piece_sets(const Handle &h, long nwg) {
+  const long ncu = std::max(1, h.ncu);
+  return nwg <= ncu ? 4 : (nwg <= 2 * ncu ? 2 : 1);
+}
+
 // Buffers of the spatial ordering for nj records and ni i-particles.
 int ensure_spatial(Handle &h, int nj, int ni) {
   const size_t n = static_cast<size_t>(std::max(nj, ni)), j = static_cast<size_t>(nj), i = static_cast<size_t>(ni);
@@ -679,6 +692,7 @@ int enqueue_calc(Handle &h, int nj, int ni, const int *d_islot, const double *d_
     // the static scratch array too small for the pieces: whole splits
     if (noalloc && calc_bytes(h.prec, false, nj, ni, npieces, minima) > scratch_bytes) pc = PieceArgs{};
     else nsplit = npieces;
+    pc.sets = piece_sets(h, static_cast<long>(nib) * npieces);
   }
   // one i-block of at most kWG: the interaction kernel predicts its tiles
   const bool fused = !one && !pc.per && use_fused(h, spatial, ipw, ni, nj);

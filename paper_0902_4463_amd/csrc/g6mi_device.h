@@ -859,14 +859,19 @@ struct NarrowLane {
       }
       if constexpr (NBL) nbm |= (m < fb ? 1u : 0u) << (k0 / kGroup);
     }
-    if constexpr (NBL) {
-      while (nbm) { // rare: append the neighbours of the flagged groups
-        const int g = __builtin_ctz(nbm);
-        nbm &= nbm - 1u;
-        for (int u = 0; u < kGroup; ++u) {
-          const int jj = sub + ((g * kGroup + u) << log2L);
-          if ((!SELF || jj != o) && r2_of<PREC>(st, tl + jj * REC) < h2) nb_append(nb_count, nb_slot, row, jbase + jj);
-        }
+    if constexpr (NBL) append_flagged(tl, jbase, nbm, o, nb_count, nb_slot);
+  }
+
+  // Rare: append the neighbours of the flagged groups (bit g of nbm: the
+  // lane's group g) of the tile at tl; o: the own slot relative to the tile.
+  __device__ __forceinline__ void append_flagged(const float4 *__restrict__ tl, int jbase, unsigned nbm, int o,
+                                                 int *__restrict__ nb_count, int *__restrict__ nb_slot) {
+    while (nbm) {
+      const int g = __builtin_ctz(nbm);
+      nbm &= nbm - 1u;
+      for (int u = 0; u < kGroup; ++u) {
+        const int jj = sub + ((g * kGroup + u) << log2L);
+        if (jj != o && r2_of<PREC>(st, tl + jj * REC) < h2) nb_append(nb_count, nb_slot, row, jbase + jj);
       }
     }
   }
@@ -885,10 +890,11 @@ struct NarrowLane {
   // synchronises before reusing it), and lane il adds parts 1 .. P - 1 in
   // order.  Afterwards the lanes with sub == 0 (tid = il) hold the
   // i-particle's totals in t and its nearest-neighbour candidate in
-  // (bestd, bslot); NN = false leaves the candidates out.
+  // (bestd, bslot); NN = false leaves the candidates out.  act = false: a lane
+  // that only takes part in the barriers (force_piece's other sets).
   template <bool NN = true>
   __device__ __forceinline__ void lane_sum(double *red, int tid, int il, int ipw, double &bestd,
-                                           int &bslot) {
+                                           int &bslot, bool act = true) {
     bestd = static_cast<double>(ebest);
     bslot = eslot;
     if (L == 1) return;
@@ -910,7 +916,7 @@ struct NarrowLane {
     if (nparts == 1) return;
     int *rslot = reinterpret_cast<int *>(red + 8 * kWG);
     __syncthreads();
-    if (tid >= stride && (tid & (stride - 1)) == il) { // holder of part tid / stride > 0
+    if (act && tid >= stride && (tid & (stride - 1)) == il) { // holder of part tid / stride > 0
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         red[d * kWG + tid] = t.acc[d];
@@ -923,7 +929,7 @@ struct NarrowLane {
       }
     }
     __syncthreads();
-    if (tid == il) {
+    if (act && tid == il) {
       for (int p = 1; p < nparts; ++p) {
         const int o = p * stride + il;
 #pragma unroll

@@ -102,11 +102,12 @@ hipError_t launch_force(int prec, bool nbl, const ForceArgs &a, int nsplit,
                         hipStream_t s);
 
 // A calculation of small blocks in pieces of its j-splits (piece_min_kernel,
-// then force_kernel): splits of vper tiles in pieces of per tiles, so that a
+// then force_piece, or force_kernel with one set): splits of vper tiles in pieces of per tiles, so that a
 // j-range too short for many splits still fills the device.  vlast: first
 // tile of the last split.
 struct PieceArgs {
   int vper = 0, per = 0, vlast = 0;
+  int sets = 1;           // sets of 256 lanes per workgroup: 1, 2 or 4 (force_piece)
   float *least = nullptr; // [tile][i-block][kWG] least softened r^2 of a lane in a tile
   float *exact = nullptr; // the same shape: exact r^2 of that group (nj not a multiple of kTile), or null
 };

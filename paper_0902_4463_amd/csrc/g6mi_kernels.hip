@@ -126,80 +126,6 @@ template <int K> struct TileRegs {
   }
 };
 
-// First launch of a calculation in pieces (PieceArgs): the predictor, and
-// each lane's least softened r^2 in each tile.  Where a group is folded into
-// the float64 totals depends on the least r^2 that the lane met before it in
-// its split (fold_or_add), so a split of eight or more tiles is one serial
-// chain; with the minima of its earlier tiles known, every piece of a split
-// can start on its own and make the same decisions.  The minima take a third
-// of the operations of the full pair.
-// Workgroup (x, y): i-block x, tile y.  i-block 0 writes the predicted
-// records; the tiles of a split's last piece need no minima.  For the split
-// that holds the ragged tile, whose lanes go by the exact r^2 found so far
-// (MaskedRun), the exact r^2 of the group holding the minimum is kept too:
-// the group that NarrowLane would resolve after the tile if it lies below
-// the minima before.  The same launch clears the neighbour counters and
-// status words.
-template <int PREC>
-__global__ __launch_bounds__(kWG) void piece_min_kernel(ForceArgs a, JMem jm, double ti, PieceArgs pc,
-                                                        float4 *__restrict__ jpred, int *__restrict__ status) {
-  static_assert(PREC != G6MI_PREC_FP64, "float64 sums do not depend on the splits");
-  constexpr int REC = rec4<PREC>();
-  __shared__ __attribute__((aligned(16))) float4 tile[kTile * REC];
-  const int tid = threadIdx.x, tt = blockIdx.y;
-  const int il = tid & (a.ipw - 1), i = blockIdx.x * a.ipw + il;
-  if (tt == 0) {
-    if (blockIdx.x == 0 && tid < kStatusWords) status[tid] = 0;
-    if (tid < a.ipw && i < a.ni) a.nb_count[i] = 0;
-  }
-  const int jbase = tt * kTile, cnt = min(kTile, a.nj - jbase);
-  const int pos = tt % pc.vper;
-  const int len = min(pc.vper, (a.nj + kTile - 1) / kTile - (tt - pos)); // tiles of the split
-  const bool need = pos / pc.per < (len - 1) / pc.per;                   // a later piece follows
-  if (blockIdx.x > 0 && !need) return;
-  if (tid < cnt) {
-    predict_record<PREC>(jm, static_cast<size_t>(jbase + tid), ti, tile + tid * REC);
-    if (blockIdx.x == 0)
-#pragma unroll
-      for (int q = 0; q < REC; ++q) jpred[static_cast<size_t>(jbase + tid) * REC + q] = tile[tid * REC + q];
-  }
-  if (!need) return;
-  IState<PREC> st;
-  int slot;
-  float h2;
-  load_i<PREC>(st, a, i, i < a.ni, slot, h2);
-  __syncthreads();
-  if (!__any(i < a.ni)) return;
-  // a tile with a later piece is full
-  const int log2L = 8 - a.log2ipw, sub = tid >> a.log2ipw, own = slot - jbase;
-  const float eps2 = static_cast<float>(a.eps2);
-  float best = INFINITY;
-  int grp = -1;
-  for (int k0 = 0; k0 < kTile >> log2L; k0 += kGroup) {
-    float m = INFINITY;
-#pragma unroll
-    for (int u = 0; u < kGroup; ++u) {
-      const int jj = sub + ((k0 + u) << log2L);
-      float d[3], w[3], mj;
-      separation<PREC>(st, tile + jj * REC, d, w, mj);
-      const float s = fma(d[2], d[2], fma(d[1], d[1], fma(d[0], d[0], eps2))); // as in pair_core
-      m = fmin(m, jj == own ? INFINITY : s);
-    }
-    if (m < best) {
-      best = m;
-      grp = jbase + sub + (k0 << log2L);
-    }
-  }
-  const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + tid;
-  pc.least[e] = best;
-  if (pc.exact && tt - pos == pc.vlast) {
-    float r2 = INFINITY;
-    int bs = -1;
-    resolve_group<PREC>(st, grp, 1 << log2L, tile, jbase, r2, bs, slot);
-    pc.exact[e] = r2;
-  }
-}
-
 // Small blocks (NarrowLane): ipw i-particles per workgroup (a power of two,
 // at most 256) and L = 256 / ipw lanes per i-particle; lane tid handles
 // i-particle (tid mod ipw) and the records sub, sub + L, ... of every tile,
@@ -274,6 +200,250 @@ __global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a, PieceArgs pc) {
   int bslot;
   n.lane_sum(reinterpret_cast<double *>(lds), tid, il, ipw, bestd, bslot);
   if (n.sub == 0 && n.valid)
+    store_part(a.part, a.nn_slot, static_cast<size_t>(blockIdx.y) * a.ni + i, n.t, bestd, bslot);
+}
+
+// First launch of a calculation in pieces (PieceArgs): the predictor, and
+// each lane's least softened r^2 in each tile.  Where a group is folded into
+// the float64 totals depends on the least r^2 that the lane met before it in
+// its split (fold_or_add), so a split of eight or more tiles is one serial
+// chain; with the minima of its earlier tiles known, every piece of a split
+// can start on its own and make the same decisions.  The minima take a third
+// of the operations of the full pair.
+// Workgroup (x, y): i-block x, tile y, S sets of 256 lanes, set k taking every
+// S-th group (see force_piece).  i-block 0 writes the predicted records; the
+// tiles of a split's last piece need no minima.  For the split that holds the
+// ragged tile, whose lanes go by the exact r^2 found so far (MaskedRun), the
+// exact r^2 of the group holding the minimum is kept too: the group that
+// NarrowLane would resolve after the tile if it lies below the minima before.
+// The same launch clears the neighbour counters and status words.
+template <int PREC, int S>
+__global__ __launch_bounds__(S * kWG) void piece_min_kernel(ForceArgs a, JMem jm, double ti, PieceArgs pc,
+                                                            float4 *__restrict__ jpred, int *__restrict__ status) {
+  static_assert(PREC != G6MI_PREC_FP64, "float64 sums do not depend on the splits");
+  constexpr int REC = rec4<PREC>();
+  __shared__ __attribute__((aligned(16))) float4 tile[kTile * REC];
+  __shared__ float s_min[S][kWG];
+  __shared__ int s_grp[S][kWG];
+  const int lid = threadIdx.x & (kWG - 1), set = S > 1 ? threadIdx.x / kWG : 0, tt = blockIdx.y;
+  const int il = lid & (a.ipw - 1), i = blockIdx.x * a.ipw + il;
+  if (tt == 0 && set == 0) {
+    if (blockIdx.x == 0 && lid < kStatusWords) status[lid] = 0;
+    if (lid < a.ipw && i < a.ni) a.nb_count[i] = 0;
+  }
+  const int jbase = tt * kTile, cnt = min(kTile, a.nj - jbase);
+  const int pos = tt % pc.vper;
+  const int len = min(pc.vper, (a.nj + kTile - 1) / kTile - (tt - pos)); // tiles of the split
+  const bool need = pos / pc.per < (len - 1) / pc.per;                   // a later piece follows
+  if (blockIdx.x > 0 && !need) return;
+  if (set == 0 && lid < cnt) {
+    predict_record<PREC>(jm, static_cast<size_t>(jbase + lid), ti, tile + lid * REC);
+    if (blockIdx.x == 0)
+#pragma unroll
+      for (int q = 0; q < REC; ++q) jpred[static_cast<size_t>(jbase + lid) * REC + q] = tile[lid * REC + q];
+  }
+  if (!need) return;
+  IState<PREC> st;
+  int slot;
+  float h2;
+  load_i<PREC>(st, a, i, i < a.ni, slot, h2);
+  __syncthreads();
+  if (S == 1 && !__any(i < a.ni)) return;
+  // a tile with a later piece is full
+  const int log2L = 8 - a.log2ipw, sub = lid >> a.log2ipw, own = slot - jbase;
+  const float eps2 = static_cast<float>(a.eps2);
+  float best = INFINITY;
+  int grp = -1;
+  const int kend = S == 1 || __any(i < a.ni) ? kTile >> log2L : 0;
+  for (int k0 = set * kGroup; k0 < kend; k0 += S * kGroup) {
+    float m = INFINITY;
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) {
+      const int jj = sub + ((k0 + u) << log2L);
+      float d[3], w[3], mj;
+      separation<PREC>(st, tile + jj * REC, d, w, mj);
+      const float s = fma(d[2], d[2], fma(d[1], d[1], fma(d[0], d[0], eps2))); // as in pair_core
+      m = fmin(m, jj == own ? INFINITY : s);
+    }
+    if (m < best) {
+      best = m;
+      grp = jbase + sub + (k0 << log2L);
+    }
+  }
+  if constexpr (S > 1) {
+    s_min[set][lid] = best;
+    s_grp[set][lid] = grp;
+    __syncthreads();
+    if (set > 0) return;
+    // the least minimum, of equal ones the first group's
+#pragma unroll
+    for (int k = 1; k < S; ++k) {
+      const float m = s_min[k][lid];
+      const int g = s_grp[k][lid];
+      if (g >= 0 && (m < best || (m == best && g < grp))) {
+        best = m;
+        grp = g;
+      }
+    }
+  }
+  const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + lid;
+  pc.least[e] = best;
+  if (pc.exact && tt - pos == pc.vlast) {
+    float r2 = INFINITY;
+    int bs = -1;
+    resolve_group<PREC>(st, grp, 1 << log2L, tile, jbase, r2, bs, slot);
+    pc.exact[e] = r2;
+  }
+}
+
+// The pieces of a calculation in pieces, after piece_min_kernel: i-blocks of
+// 32 to 256 i-particles as in force_kernel, S sets of 256 lanes per workgroup.
+// The lanes of one set are those of force_kernel; set k evaluates every S-th
+// group of kGroup records of their chains (k, k + S, ...), and set 0 adds the
+// group sums of a round in order, through LDS, by the rule of fold_or_add.  A
+// block of a few hundred i-particles against 2^15 records is one workgroup
+// per compute unit: with one set the chains' latency is exposed (341 against
+// 2^15 in double-single: this kernel 38.5 us with one set, 23.9 with four,
+// piece_min_kernel 18.8 and 12.9).
+// Grid: x = i-blocks, y = pieces, one split after the other; each starts from
+// the minima of its split's earlier tiles.  The double buffer lets the other
+// sets go on to the next round while set 0 adds.
+template <int PREC, bool NBL, int S>
+__global__ __launch_bounds__(S * kWG, 4) void force_piece(ForceArgs a, PieceArgs pc) {
+  constexpr int REC = rec4<PREC>();
+  constexpr int kTileBytes = kTile * REC * 16;
+  constexpr int kXBytes = 2 * (S - 1) * kWG * 48;
+  static_assert(kXBytes >= kWG * 9 * 8, "the lane sums reuse the exchange area");
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kTileBytes + kXBytes];
+  float4 *tile = reinterpret_cast<float4 *>(lds);
+  // group sums of sets 1 .. S - 1: [buffer][set - 1][lane][3]: a, min; j1, p; j2, slot
+  float4 *xch = reinterpret_cast<float4 *>(lds + kTileBytes);
+
+  const int tid = threadIdx.x, lid = tid & (kWG - 1);
+  const int set = __builtin_amdgcn_readfirstlane(tid / kWG);
+  const int ipw = a.ipw, il = lid & (ipw - 1), i = blockIdx.x * ipw + il;
+  NarrowLane<PREC, NBL> n;
+  n.init(a, i, i < a.ni, lid >> a.log2ipw, 8 - a.log2ipw);
+  const float eps2 = static_cast<float>(a.eps2);
+  const bool busy = __any(n.valid); // whole waves without an i-particle have no work
+
+  const int ntiles = (a.nj + kTile - 1) / kTile;
+  const float4 *jp = static_cast<const float4 *>(a.jpred);
+  const int ppv = (pc.vper + pc.per - 1) / pc.per; // pieces per split
+  const int v0 = static_cast<int>(blockIdx.y) / ppv * pc.vper;
+  const int tb = v0 + static_cast<int>(blockIdx.y) % ppv * pc.per;
+  const int te = min(min(ntiles, v0 + pc.vper), tb + pc.per);
+  if (set == 0)
+    for (int tt = v0; tt < min(tb, te); ++tt) {
+      const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + lid;
+      const float m = pc.least[e];
+      if (m < n.gbest) {
+        n.gbest = m;
+        if (pc.exact && v0 == pc.vlast) n.ebest = fminf(n.ebest, pc.exact[e]);
+      }
+    }
+
+  for (int tt = tb; tt < te; ++tt) {
+    const int jbase = tt * kTile;
+    const int cnt = min(kTile, a.nj - jbase);
+    __syncthreads();
+    for (int q = tid; q < cnt * REC; q += S * kWG) tile[q] = jp[static_cast<size_t>(jbase) * REC + q];
+    __syncthreads();
+    const bool ragged = cnt < kTile;
+    const int L = n.L, rounds = (n.K / kGroup + S - 1) / S;
+    const int own = n.slot - jbase; // own slot relative to the tile
+    const bool self = __any(own >= 0 && own < cnt);
+    const float fb = nb_flag_bound(n.h2, eps2);
+    unsigned nbm = 0u;
+    for (int r = 0; r < rounds; ++r) {
+      const int k0 = (r * S + set) * kGroup; // first record of this set's group in the lane's chain
+      Sums<float> gs;
+      float m = INFINITY;
+      int bs = -1, got = 0; // a ragged tile: the slot at the minimum, records in the group
+      if (busy && !ragged) {
+        auto group = [&](auto masked) {
+          constexpr bool SELF = decltype(masked)::value;
+          int jj = n.sub + (k0 << n.log2L);
+          m = pair_core<PREC, true, SELF>(n.st, gs, tile + jj * REC, eps2, jj == own);
+#pragma unroll
+          for (int u = 1; u < kGroup; ++u) {
+            jj = n.sub + ((k0 + u) << n.log2L);
+            m = fmin(m, pair_core<PREC, false, SELF>(n.st, gs, tile + jj * REC, eps2, jj == own));
+          }
+        };
+        if (self) group(std::true_type{});
+        else group(std::false_type{});
+        got = kGroup;
+      } else if (busy) {
+        // per pair, with the exact r^2, as in MaskedRun
+        gs.zero();
+        int *cp = a.nb_count + (n.valid ? n.row : 0);
+        int *lp = a.nb_slot + static_cast<size_t>(n.valid ? n.row : 0) * kNbMax;
+        for (int u = 0; u < kGroup; ++u) {
+          const int jj = n.sub + ((k0 + u) << n.log2L);
+          if (jj < cnt) {
+            pair<PREC, true, NBL>(n.st, gs, tile + jj * REC, jbase + jj, n.slot, eps2, n.h2, m, bs, cp, lp);
+            ++got;
+          }
+        }
+      }
+      float4 *x = xch + static_cast<size_t>(r & 1) * (S - 1) * kWG * 3;
+      if (set > 0 && busy) {
+        float4 *o = x + ((set - 1) * kWG + lid) * 3;
+        o[0] = make_float4(gs.a[0], gs.a[1], gs.a[2], m);
+        o[1] = make_float4(gs.j1[0], gs.j1[1], gs.j1[2], gs.p);
+        o[2] = make_float4(gs.j2[0], gs.j2[1], gs.j2[2], __int_as_float(bs));
+      }
+      __syncthreads();
+      if (set == 0 && busy) {
+        // the round's groups in the order of the records
+        auto take = [&](Sums<float> &g, float mg, int slot, int k, int records) {
+          if (!ragged) {
+            fold_or_add(g, n.ts, n.t, mg < n.gbest);
+            if (mg < n.gbest) {
+              n.gbest = mg;
+              n.grp = jbase + n.sub + (k << n.log2L);
+            }
+            if constexpr (NBL) nbm |= (mg < fb ? 1u : 0u) << (k / kGroup);
+          } else if (records > 0) {
+            if (records == kGroup) fold_or_add(g, n.ts, n.t, mg < n.ebest);
+            else n.ts.add(g);
+            if (mg < n.ebest) {
+              n.ebest = mg;
+              n.eslot = slot;
+            }
+          }
+        };
+        take(gs, m, bs, k0, got);
+#pragma unroll
+        for (int k = 1; k < S; ++k) {
+          const int kk = (r * S + k) * kGroup;
+          if (kk < n.K) {
+            const float4 *o = x + ((k - 1) * kWG + lid) * 3;
+            const float4 q0 = o[0], q1 = o[1], q2 = o[2];
+            Sums<float> g;
+            g.a[0] = q0.x; g.a[1] = q0.y; g.a[2] = q0.z;
+            g.j1[0] = q1.x; g.j1[1] = q1.y; g.j1[2] = q1.z;
+            g.p = q1.w;
+            g.j2[0] = q2.x; g.j2[1] = q2.y; g.j2[2] = q2.z;
+            // records of that group in this lane's chain
+            const int rest = (cnt - n.sub + L - 1) / L - kk;
+            take(g, q0.w, __float_as_int(q2.w), kk, min(rest, kGroup));
+          }
+        }
+      }
+    }
+    if (set == 0 && busy) {
+      fold(n.ts, n.t);
+      if constexpr (NBL) n.append_flagged(tile, jbase, nbm, own, a.nb_count, a.nb_slot);
+      n.resolve(tile, jbase); // while the tile is still in LDS
+    }
+  }
+
+  double bestd;
+  int bslot;
+  n.lane_sum(reinterpret_cast<double *>(xch), lid, il, ipw, bestd, bslot, set == 0);
+  if (set == 0 && n.sub == 0 && n.valid)
     store_part(a.part, a.nn_slot, static_cast<size_t>(blockIdx.y) * a.ni + i, n.t, bestd, bslot);
 }
 
@@ -692,23 +862,41 @@ hipError_t launch_force(int prec, bool nbl, const ForceArgs &a, int nsplit, hipS
   return hipGetLastError();
 }
 
-template <int PREC>
-static void launch_pieces_prec(bool nbl, const ForceArgs &a, const JMem &jm, double ti, const PieceArgs &pc,
+template <int PREC, int S>
+static void launch_pieces_sets(bool nbl, const ForceArgs &a, const JMem &jm, double ti, const PieceArgs &pc,
                                void *jpred, int *status, int npieces, hipStream_t s) {
   const unsigned nib = static_cast<unsigned>((a.ni + a.ipw - 1) / a.ipw);
   const unsigned ntiles = static_cast<unsigned>((a.nj + kTile - 1) / kTile);
-  hipLaunchKernelGGL(piece_min_kernel<PREC>, dim3(nib, ntiles), dim3(kWG), 0, s, a, jm, ti, pc,
+  hipLaunchKernelGGL((piece_min_kernel<PREC, S>), dim3(nib, ntiles), dim3(S * kWG), 0, s, a, jm, ti, pc,
                      static_cast<float4 *>(jpred), status);
   const dim3 grid(nib, static_cast<unsigned>(npieces));
-  if (nbl)
-    hipLaunchKernelGGL((force_kernel<PREC, true, true>), grid, dim3(kWG), 0, s, a, pc);
+  if constexpr (S == 1) {
+    if (nbl)
+      hipLaunchKernelGGL((force_kernel<PREC, true, true>), grid, dim3(kWG), 0, s, a, pc);
+    else
+      hipLaunchKernelGGL((force_kernel<PREC, false, true>), grid, dim3(kWG), 0, s, a, pc);
+  } else if (nbl)
+    hipLaunchKernelGGL((force_piece<PREC, true, S>), grid, dim3(S * kWG), 0, s, a, pc);
   else
-    hipLaunchKernelGGL((force_kernel<PREC, false, true>), grid, dim3(kWG), 0, s, a, pc);
+    hipLaunchKernelGGL((force_piece<PREC, false, S>), grid, dim3(S * kWG), 0, s, a, pc);
+}
+
+// pc.sets: one, two, or four where a lane's chain has four groups in a tile
+// (64 i-particles per workgroup and more).
+template <int PREC>
+static void launch_pieces_prec(bool nbl, const ForceArgs &a, const JMem &jm, double ti, const PieceArgs &pc,
+                               void *jpred, int *status, int npieces, hipStream_t s) {
+  if (pc.sets == 4 && a.ipw * 4 >= kWG)
+    launch_pieces_sets<PREC, 4>(nbl, a, jm, ti, pc, jpred, status, npieces, s);
+  else if (pc.sets > 1)
+    launch_pieces_sets<PREC, 2>(nbl, a, jm, ti, pc, jpred, status, npieces, s);
+  else
+    launch_pieces_sets<PREC, 1>(nbl, a, jm, ti, pc, jpred, status, npieces, s);
 }
 
 hipError_t launch_force_pieces(int prec, bool nbl, const ForceArgs &a, const JMem &jm, double ti,
                                const PieceArgs &pc, void *jpred, int *status, int npieces, hipStream_t s) {
-  if (a.ni <= 0 || a.nj <= 0 || a.ipw > kWG || a.ipw < 1 || pc.per < 1 || pc.vper < pc.per || !pc.least)
+  if (a.ni <= 0 || a.nj <= 0 || a.ipw > kWG || a.ipw < 32 || pc.per < 1 || pc.vper < pc.per || !pc.least)
     return hipErrorInvalidValue;
   if (prec == G6MI_PREC_DS) launch_pieces_prec<G6MI_PREC_DS>(nbl, a, jm, ti, pc, jpred, status, npieces, s);
   else if (prec == G6MI_PREC_FP32) launch_pieces_prec<G6MI_PREC_FP32>(nbl, a, jm, ti, pc, jpred, status, npieces, s);

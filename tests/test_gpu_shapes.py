@@ -66,11 +66,12 @@ def test_split_count_of_small_blocks(prec, ni, n):
 
 
 @pytest.mark.parametrize("prec", ["ds", "fp32"])
-@pytest.mark.parametrize("ni", [17, 33, 100, 256, 300, 511])
-@pytest.mark.parametrize("n", [257, 600, 1024, 4097, 5100, 33000])
-def test_pieces_match_whole_splits(prec, ni, n):
-    """Blocks of 17 to 511 in pieces of their j-splits, each starting from the
-    minima of its split's earlier tiles, against the same splits walked whole
+@pytest.mark.parametrize("n,ni", [(n, ni) for n in (257, 600, 1024, 4097, 5100, 33000)
+                                  for ni in (17, 33, 100, 256, 300, 511)] + [(140000, 20), (140001, 100)])
+def test_pieces_match_whole_splits(prec, n, ni):
+    """Blocks of 17 to 511 in pieces of their j-splits, with one, two and four
+    sets of lanes per workgroup (many pieces, more than one per compute unit,
+    few), each starting from the minima of its split's earlier tiles, against the same splits walked whole
     (a shape set by hand).  Ragged last tiles, own slots in nearly every tile,
     no softening, lists near and far."""
     import paper_0902_4463_amd as g6
