@@ -28,33 +28,67 @@ namespace g6mi {
 
 // -------------------------------------------------------------------- plan
 
-// Inclusive sum of x over the 256 threads of a workgroup (wave shuffles, then
-// the four wave totals through LDS); all = the workgroup total.  Every
-// thread must call it; it ends with a barrier, so s_part can be reused.
-template <class T> __device__ __forceinline__ T wg_scan(T x, T *s_part, T &all) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const T y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
-  if (lane == 63) s_part[wave] = x;
-  __syncthreads();
-  T base = 0, sum = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const T p = s_part[w];
-    if (w < wave) base += p;
-    sum += p;
-  }
-  __syncthreads();
-  all = sum;
-  return x + base;
+// Threads of the plan kernel: one workgroup fills the work tables, whose time
+// is the latency of its passes (cold instruction fetch, scans, divisions,
+// binary searches), one cluster per thread and pass.  256 threads for up to
+// kPlanFew clusters, 1024 for more: 24 clusters 6.9 us (9.3 before the wave
+// scans below, the single scan per pass and the 32-bit divisions), 65 clusters
+// 9.9 (9.9), 256 clusters 11.0 (12.4), 364 clusters 11.5 (21.8: every pass
+// twice), 1000 clusters 12.9 (38.5).
+constexpr int kPlanFew = 64;
+
+// One step of a wave scan on the VALU's lane-shift paths (a cross-lane
+// exchange through LDS has several times their latency): x plus the value of
+// the lane the control names, zero where it names none.
+template <int CTRL, int ROWS> __device__ __forceinline__ long long dpp_add(long long x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(x >> 32), CTRL, ROWS, 0xf, false);
+  return x + ((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+}
+// Inclusive sum over the 64 lanes of a wave: shifts by 1, 2, 4 and 8 inside
+// rows of 16, then the last lane of a row added to the next (rows 1 and 3),
+// and of lane 31 to the upper half.
+__device__ __forceinline__ long long wave_scan(long long x) {
+  x = dpp_add<0x111, 0xf>(x);
+  x = dpp_add<0x112, 0xf>(x);
+  x = dpp_add<0x114, 0xf>(x);
+  x = dpp_add<0x118, 0xf>(x);
+  x = dpp_add<0x142, 0xa>(x);
+  return dpp_add<0x143, 0xc>(x);
 }
 
-// Index of the first of 256 non-decreasing counts above q (one exists).
-__device__ __forceinline__ int first_above(const int *inc, int q) {
-  int lo = 0, hi = 255;
+// Inclusive sums of N values per thread over the workgroup (wave scans, then
+// the wave totals through LDS, s_part[N * WG / 64]); all = the totals.
+// Every thread must call it; it ends with a barrier, so s_part can be reused.
+template <int WG, int N>
+__device__ __forceinline__ void wg_scan(long long (&x)[N], long long *s_part, long long (&all)[N]) {
+  constexpr int kWaves = WG / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    x[k] = wave_scan(x[k]);
+    if (lane == 63) s_part[k * kWaves + wave] = x[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    // lane w of every wave holds the total of wave w
+    const long long t = wave_scan(lane < kWaves ? s_part[k * kWaves + lane] : 0);
+    auto at = [&](int w) {
+      const int lo = __builtin_amdgcn_readlane(static_cast<int>(t), w);
+      const int hi = __builtin_amdgcn_readlane(static_cast<int>(t >> 32), w);
+      return (static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo);
+    };
+    all[k] = at(63);
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    if (w > 0) x[k] += at(w - 1);
+  }
+  __syncthreads();
+}
+
+// Index of the first of WG non-decreasing counts above q (one exists).
+template <int WG> __device__ __forceinline__ int first_above(const int *inc, int q) {
+  int lo = 0, hi = WG - 1;
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
     if (inc[mid] > q) hi = mid;
@@ -76,36 +110,37 @@ __device__ __forceinline__ int first_above(const int *inc, int q) {
 // Pass 1 checks the descriptors, picks the block shape of each cluster
 // (kept in its plan entry) and adds up the batch's work; pass 1b cuts the
 // blocks of clusters too small to fill their share of the GPU; pass 2 picks
-// the splits, scans i-blocks and partial entries and fills the i-block ->
-// cluster table; pass 3 scans the items class by class (plan_order) and
-// fills the item -> cluster table.
-__global__ __launch_bounds__(256) void batch_plan_kernel(BatchArgs b) {
+// the splits, scans i-blocks, partial entries and the items of each queue
+// class (plan_order) and fills the i-block -> cluster table; pass 3 puts the
+// classes one after the other and fills the item -> cluster table.
+// With at most WG clusters (one chunk) each thread keeps its cluster's entry in
+// registers from pass to pass; with more, it reads back its own entry of each
+// chunk.
+template <int WG>
+__global__ __launch_bounds__(WG) void batch_plan_kernel(BatchArgs b) {
   const int tid = threadIdx.x;
   if (blockIdx.x > 0) {
     // rows (blockIdx.x - 1) * chunk ...: neighbour counts
     const int base = (blockIdx.x - 1) * kPlanZeroChunk;
     if (b.nbl)
-      for (int k = tid; k < kPlanZeroChunk; k += 256) {
+      for (int k = tid; k < kPlanZeroChunk; k += WG) {
         const int r = base + k;
         if (r < b.ni_total) b.fa.nb_count[r] = 0;
       }
     return;
   }
-  __shared__ long long s_part[4];
-  __shared__ int s_inc[256], s_inc_ib[256];
+  __shared__ long long s_part[4 * WG / 64];
+  __shared__ int s_inc[kItemOrders][WG], s_inc_ib[WG];
   __shared__ int s_flags;
   if (tid == 0) s_flags = 0;
   __syncthreads();
 
-  // With one chunk (ncl <= 256) each thread keeps its cluster's entry in
-  // registers from pass to pass (pl_last), instead of a round trip through
-  // memory per pass; with more, it reads back its own entry of each chunk.
   BatchPlan pl_last{};
-  const bool one_chunk = b.ncl <= 256;
+  const bool one_chunk = b.ncl <= WG;
 
   // pass 1: validity, block shape, work
   long long c_rows = 0, work = 0;
-  for (int c0 = 0; c0 < b.ncl; c0 += 256) {
+  for (int c0 = 0; c0 < b.ncl; c0 += WG) {
     const int c = c0 + tid;
     int ni = 0, nj = 0;
     bool ok = false;
@@ -117,101 +152,140 @@ __global__ __launch_bounds__(256) void batch_plan_kernel(BatchArgs b) {
       ni = ok ? d.ni : 0;
       nj = ok ? d.nj : 0;
     }
+    BatchPlan pl = plan_shape(ni, nj, b.tune); // splits in pass 2
+    long long sum[2] = {ni, plan_work(pl)}, all[2];
+    wg_scan<WG>(sum, s_part, all);
     // Clusters sharing i-rows could add up to more rows than ni_total, and
     // the i-block counters and partial sums are sized by ni_total: every
     // cluster past that many rows in total is skipped.
-    long long rows_all;
-    const long long rows = wg_scan<long long>(ni, s_part, rows_all);
-    if (ok && c_rows + rows > b.ni_total) {
-      ok = false;
-      ni = nj = 0;
+    if (c_rows + all[0] > b.ni_total) {
+      if (ok && c_rows + sum[0] > b.ni_total) {
+        ok = false;
+        pl = plan_shape(0, 0, b.tune);
+      }
+      long long kept[1] = {plan_work(pl)}, kept_all[1];
+      wg_scan<WG>(kept, s_part, kept_all);
+      all[1] = kept_all[0];
     }
     if (c < b.ncl && !ok) atomicOr(&s_flags, kFlagBadCluster);
-    const BatchPlan pl = plan_shape(ni, nj, b.tune); // splits in pass 2
-    if (c < b.ncl) b.plan[c] = pl;
+    if (c < b.ncl && !one_chunk) b.plan[c] = pl;
     pl_last = pl;
-    long long work_all;
-    wg_scan<long long>(plan_work(pl), s_part, work_all);
-    work += work_all;
-    c_rows += rows_all;
+    work += all[1];
+    c_rows += all[0];
   }
   // pass 1b: clusters too small for their share of the persistent
   // workgroups (plan_share); the share is the grid times the cluster's
   // fraction of the batch's work
   const long long work0 = max(1LL, work);
   work = 0;
-  for (int c0 = 0; c0 < b.ncl; c0 += 256) {
+  for (int c0 = 0; c0 < b.ncl; c0 += WG) {
     const int c = c0 + tid;
-    long long w = 0;
+    long long w[1] = {0}, all[1];
     if (c < b.ncl) {
       BatchPlan pl = one_chunk ? pl_last : b.plan[c];
       if (pl.nib > 0) {
-        const long long share = (static_cast<long long>(b.grid) * plan_work(pl) + work0 - 1) / work0;
-        if (plan_share(pl, share, b.tune)) b.plan[c] = pl;
-        w = plan_work(pl);
+        const long long share = plan_div(static_cast<long long>(b.grid) * plan_work(pl) + work0 - 1, work0);
+        if (plan_share(pl, share, b.tune) && !one_chunk) b.plan[c] = pl;
+        w[0] = plan_work(pl);
       }
       pl_last = pl;
     }
-    long long work_all;
-    wg_scan<long long>(w, s_part, work_all);
-    work += work_all;
+    wg_scan<WG>(w, s_part, all);
+    work += all[0];
   }
   const long long target = plan_target(work, b.grid, b.tune);
 
-  // pass 2: splits, the i-block and partial-entry scans in cluster order
-  // (each thread reads back its own pass-1 entries) and the i-block ->
+  // pass 2: splits, the scans of i-blocks and partial entries in cluster order
+  // and of the items of each queue class (plan_order), and the i-block ->
   // cluster table, filled by all threads: i-block q of the chunk belongs to
-  // the first cluster whose inclusive i-block count exceeds q
-  int c_nib = 0;
+  // the first cluster whose inclusive i-block count exceeds q.  item0 is
+  // counted inside the class until the classes' totals are known.  Classes 0
+  // and 1 share a scanned word (fewer than 2^31 items each).
+  int c_nib = 0, c_class[kItemOrders] = {0, 0, 0};
   long long c_pent = 0;
-  for (int c0 = 0; c0 < b.ncl; c0 += 256) {
+  static_assert(kItemOrders == 3, "three classes in two scanned words");
+  for (int c0 = 0; c0 < b.ncl; c0 += WG) {
     const int c = c0 + tid;
-    int nib = 0, ni = 0, nsplit = 1;
     BatchPlan pl{};
+    int n[kItemOrders] = {0, 0, 0}, order = 0;
     if (c < b.ncl) {
       pl = one_chunk ? pl_last : b.plan[c];
       plan_splits(pl, target, b.tune);
-      nib = pl.nib;
-      ni = pl.ni;
-      nsplit = pl.nsplit;
+      order = plan_order(pl);
+#pragma unroll
+      for (int k = 0; k < kItemOrders; ++k) n[k] = order == k ? pl.nib * pl.nsplit : 0;
     }
-    const long long pent = static_cast<long long>(ni) * nsplit;
-    long long nib_all, pent_all;
-    const int nibs = static_cast<int>(wg_scan<long long>(nib, s_part, nib_all));
-    const long long pents = wg_scan<long long>(pent, s_part, pent_all);
+    const long long pent = static_cast<long long>(pl.ni) * pl.nsplit;
+    long long sum[4] = {pl.nib, pent, n[0] + (static_cast<long long>(n[1]) << 32), n[2]}, all[4];
+    wg_scan<WG>(sum, s_part, all);
+    const int inc[kItemOrders] = {static_cast<int>(sum[2]), static_cast<int>(sum[2] >> 32), static_cast<int>(sum[3])};
+    const int tot[kItemOrders] = {static_cast<int>(all[2]), static_cast<int>(all[2] >> 32), static_cast<int>(all[3])};
     if (c < b.ncl) {
-      pl.ib0 = c_nib + nibs - nib;
-      pl.pbase = c_pent + pents - pent;
-      b.plan[c] = pl;
+      pl.ib0 = c_nib + static_cast<int>(sum[0]) - pl.nib;
+      pl.pbase = c_pent + sum[1] - pent;
+#pragma unroll
+      for (int k = 0; k < kItemOrders; ++k)
+        if (order == k) pl.item0 = c_class[k] + inc[k] - n[k];
+      if (!one_chunk) b.plan[c] = pl;
     }
     pl_last = pl;
-    s_inc_ib[tid] = nibs;
+    s_inc_ib[tid] = static_cast<int>(sum[0]);
+    if (one_chunk)
+#pragma unroll
+      for (int k = 0; k < kItemOrders; ++k) s_inc[k][tid] = inc[k];
     __syncthreads();
-    for (int q = tid; q < nib_all; q += 256) b.ib_cl[c_nib + q] = c0 + first_above(s_inc_ib, q);
+    for (int q = tid; q < static_cast<int>(all[0]); q += WG) b.ib_cl[c_nib + q] = c0 + first_above<WG>(s_inc_ib, q);
     __syncthreads(); // s_inc_ib is rewritten by the next chunk
-    c_nib += static_cast<int>(nib_all);
-    c_pent += pent_all;
+    c_nib += static_cast<int>(all[0]);
+    c_pent += all[1];
+#pragma unroll
+    for (int k = 0; k < kItemOrders; ++k) c_class[k] += tot[k];
   }
-  // pass 3: the item scan and the item -> cluster table, one queue class
-  // (plan_order) after the other, in cluster order within a class
-  int c_items = 0;
-  for (int k = 0; k < kItemOrders; ++k) {
-    for (int c0 = 0; c0 < b.ncl; c0 += 256) {
+  // pass 3: each cluster's items put after the classes before its own, and the
+  // item -> cluster table, one class after the other, in cluster order within
+  // a class
+  const int base[kItemOrders] = {0, c_class[0], c_class[0] + c_class[1]};
+  const int c_items = base[2] + c_class[2];
+  if (one_chunk) {
+    if (tid < b.ncl) {
+#pragma unroll
+      for (int k = 0; k < kItemOrders; ++k)
+        if (plan_order(pl_last) == k) pl_last.item0 += base[k];
+      b.plan[tid] = pl_last;
+    }
+    for (int q = tid; q < min(c_items, b.item_cap); q += WG) {
+      const int k = q >= base[2] ? 2 : (q >= base[1] ? 1 : 0);
+      b.item_cl[q] = first_above<WG>(s_inc[k], q - (k == 2 ? base[2] : (k == 1 ? base[1] : 0)));
+    }
+  } else {
+    int done[kItemOrders] = {0, 0, 0}; // items of each class in the chunks before
+    for (int c0 = 0; c0 < b.ncl; c0 += WG) {
       const int c = c0 + tid;
-      long long n = 0;
+      BatchPlan pl{};
+      int order = -1;
       if (c < b.ncl) {
-        const BatchPlan pl = one_chunk ? pl_last : b.plan[c];
-        if (plan_order(pl) == k) n = static_cast<long long>(pl.nib) * pl.nsplit;
+        pl = b.plan[c];
+        order = plan_order(pl);
       }
-      long long items_all;
-      const int items = static_cast<int>(wg_scan<long long>(n, s_part, items_all));
-      if (n > 0) b.plan[c].item0 = c_items + items - static_cast<int>(n);
-      s_inc[tid] = items;
+      const int n = pl.nib * pl.nsplit;
+      // inclusive counts inside the chunk, by class: a thread of another class
+      // repeats the count before it
+      long long sum[2] = {order == 0 ? n : (order == 1 ? static_cast<long long>(n) << 32 : 0), order == 2 ? n : 0};
+      long long all[2];
+      wg_scan<WG>(sum, s_part, all);
+      s_inc[0][tid] = static_cast<int>(sum[0]);
+      s_inc[1][tid] = static_cast<int>(sum[0] >> 32);
+      s_inc[2][tid] = static_cast<int>(sum[1]);
+      const int tot[kItemOrders] = {static_cast<int>(all[0]), static_cast<int>(all[0] >> 32), static_cast<int>(all[1])};
       __syncthreads();
-      for (int q = tid; q < items_all; q += 256)
-        if (c_items + q < b.item_cap) b.item_cl[c_items + q] = c0 + first_above(s_inc, q);
+#pragma unroll
+      for (int k = 0; k < kItemOrders; ++k) {
+        if (order == k) b.plan[c].item0 = base[k] + pl.item0;
+        for (int q = tid; q < tot[k]; q += WG)
+          if (base[k] + done[k] + q < b.item_cap) b.item_cl[base[k] + done[k] + q] = c0 + first_above<WG>(s_inc[k], q);
+        done[k] += tot[k];
+      }
       __syncthreads(); // s_inc is rewritten by the next chunk
-      c_items += static_cast<int>(items_all);
     }
   }
   if (tid == 0) {
@@ -367,7 +441,10 @@ __global__ __launch_bounds__(kWG) void batch_nb_exact_kernel(BatchArgs b) {
 
 hipError_t launch_batch_plan(const BatchArgs &b, hipStream_t s) {
   const unsigned zero_blocks = static_cast<unsigned>((b.ni_total + kPlanZeroChunk - 1) / kPlanZeroChunk);
-  hipLaunchKernelGGL(batch_plan_kernel, dim3(1 + zero_blocks), dim3(256), 0, s, b);
+  if (b.ncl <= kPlanFew)
+    hipLaunchKernelGGL(batch_plan_kernel<256>, dim3(1 + zero_blocks), dim3(256), 0, s, b);
+  else
+    hipLaunchKernelGGL(batch_plan_kernel<1024>, dim3(1 + zero_blocks), dim3(1024), 0, s, b);
   return hipGetLastError();
 }
 

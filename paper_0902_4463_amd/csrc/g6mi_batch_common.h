@@ -58,17 +58,24 @@ __host__ __device__ __forceinline__ bool plan_share(BatchPlan &pl, long long sha
   return true;
 }
 
+// a / b for a >= 0, b > 0: in 32 bits where both fit (the usual batch; a
+// 64-bit division is some 150 dependent instructions).
+__host__ __device__ __forceinline__ long long plan_div(long long a, long long b) {
+  if (((a | b) >> 32) == 0) return static_cast<unsigned>(a) / static_cast<unsigned>(b);
+  return a / b;
+}
+
 // Item target in lane-pairs: item_work * 128, lowered (down to one) until
 // the batch's work makes about one item per persistent workgroup.
 __host__ __device__ __forceinline__ long long plan_target(long long work, int grid, const BatchTune &t) {
-  return max(1LL, min(static_cast<long long>(t.item_work) * 128, work / max(1, grid)));
+  return max(1LL, min(static_cast<long long>(t.item_work) * 128, plan_div(work, max(1, grid))));
 }
 
 // Tiles per split and split count of a shaped cluster for the item target,
 // at most max_split splits.
 __host__ __device__ __forceinline__ void plan_splits(BatchPlan &pl, long long target, const BatchTune &t) {
   const int ntiles = pl.per;
-  int per = static_cast<int>(max(1LL, min(static_cast<long long>(max(ntiles, 1)), target / pl.ipw)));
+  int per = static_cast<int>(max(1LL, min(static_cast<long long>(max(ntiles, 1)), target >> pl.log2ipw)));
   int nsplit = ntiles > 0 ? (ntiles + per - 1) / per : 1;
   if (nsplit > t.max_split) {
     per = (ntiles + t.max_split - 1) / t.max_split;
