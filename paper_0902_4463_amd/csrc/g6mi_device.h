@@ -765,6 +765,32 @@ struct WideLanes {
   }
 };
 
+// ------------------------------- waves of partly filled i-blocks
+
+// Place of thread t in its set of kWG lanes, the waves of set k turned by k:
+// wave w of a workgroup runs on SIMD w mod 4, so without the turn the waves
+// left empty by a partly filled i-block are the same SIMD's in every set.
+__device__ __forceinline__ int turned_lane(int t, int set) { return (t + (set << 6)) & (kWG - 1); }
+
+// First row of i-block b of nib: with one lane per i-particle (ipw = kWG) the
+// block's waves of 64 rows are dealt evenly, else ipw rows to each.  The
+// largest i-block sets the time of a launch that fits the device at once: 341
+// rows go as 192 and 149 instead of 256 and 85 (against 32768, with the turn
+// above, force_piece 24.3 -> 21.6 us and piece_min_kernel 13.0 -> 12.1), 300
+// rows as 192 and 108 (against 200000 in float32 155 -> 134 us per call), 560
+// as three blocks of 192 or less (against 200000 158 -> 151 us).
+__device__ __forceinline__ int first_row(const ForceArgs &a, int b, int nib) {
+  if (a.ipw != kWG) return b * a.ipw;
+  const int waves = (a.ni + 63) >> 6, q = waves / nib, r = waves - q * nib;
+  return 64 * (b * q + min(b, r));
+}
+// The workgroup's i-block (x of the grid): its rows [first, end).
+struct BlockRows {
+  int first, end;
+  __device__ __forceinline__ BlockRows(const ForceArgs &a)
+      : first(first_row(a, blockIdx.x, gridDim.x)), end(min(a.ni, first_row(a, blockIdx.x + 1, gridDim.x))) {}
+};
+
 // ------------------------------------- one i-particle on L lanes
 
 // Lane state of a narrow block: ipw i-particles per workgroup (a power of

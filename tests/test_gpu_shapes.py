@@ -93,6 +93,24 @@ def test_pieces_match_whole_splits(prec, n, ni):
     assert_same_sums(a, b)
 
 
+@pytest.mark.parametrize("prec", ["ds", "fp32", "fp64"])
+@pytest.mark.parametrize("ni", [129, 192, 257, 300, 341, 449, 512, 513, 640, 1025])
+def test_waves_dealt_over_i_blocks(prec, ni):
+    """i-blocks of 256 share the block's waves of 64 rows evenly: the same
+    rows as 64 at a time."""
+    import paper_0902_4463_amd as g6
+    jm = workloads.random_cluster(1300, seed=4400)
+    slots = workloads.active_set(jm.n, ni, seed=ni)
+    with g6.Session(4, precision=prec) as s:
+        s.load(jm)
+        xi, vi = jm.x[slots], jm.v[slots]
+        a = evaluate(g6, s, jm, slots, xi, vi, 1e-6, 0.02, (256, 2))
+        parts = [evaluate(g6, s, jm, slots[k:k + 64], xi[k:k + 64], vi[k:k + 64], 1e-6, 0.02, (256, 2))
+                 for k in range(0, ni, 64)]
+    keys = ("acc", "jerk", "pot", "nn_index", "nn_r2", "nb_count", "nb_list")
+    assert_same_sums(a, {k: np.concatenate([p[k] for p in parts]) for k in keys})
+
+
 @pytest.mark.parametrize("ni,changed", [(1, 1), (17, 0), (341, 341), (1024, 700), (1025, 3), (1500, 2500)])
 def test_host_calls_with_and_without_copies(ni, changed):
     """Host calls whose inputs and results travel through pinned memory
