@@ -258,8 +258,9 @@ int g6mi_set_fused_predict(int id, int on);
  * G6MI_EINVAL. */
 int g6mi_set_shape(int id, int i_per_group, int j_splits);
 
-/* Launch shape used by the last calculation: i per workgroup, j-splits,
- * j per tile, workgroups.  Returns 0 or a negative code. */
+/* Launch shape used by the last calculation: i per workgroup, j-splits
+ * (pieces of splits where a small block is cut further), j per tile,
+ * workgroups.  Returns 0 or a negative code. */
 int g6mi_get_shape(int id, int shape[4]);
 
 /* Enable (1) or disable (0, default) per-kernel timing with HIP events
@@ -449,8 +450,8 @@ int g6mi_batch_autotune(int id, int ncl, const g6mi_cluster *cl,
 /* ------------------------------------------- device-resident block steps
  *
  * The client side of Sec. 2.1 (i-prediction, Hermite corrector, block time
- * steps) run on the GPU, so that a whole block step is one replayed graph
- * of four kernels with no host round trip.  The particles are j-slots
+ * steps) run on the GPU, so that a whole block step is three kernels of a
+ * replayed graph with no host round trip.  The particles are j-slots
  * 0 .. n-1 of handle id: their t, mass, x, v and index as last set (all t
  * equal); the integrator then owns those slots and updates them in place
  * (position, velocity, a/2, jerk/6, time) after every step.

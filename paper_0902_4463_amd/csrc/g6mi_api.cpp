@@ -406,27 +406,34 @@ int few_splits(int prec, int ipw) {
 
 // Tiles per split of force_one over nib i-blocks of 256 and ntiles tiles: the
 // choice with the least modelled time, in units of a tile's time with four
-// workgroups on each compute unit (53 us in double-single, 44 us in float32,
-// 88 us in float64).  Workgroups run in rounds of four per compute unit; a
-// last round of k per compute unit takes the fraction below of a full one
-// (latency-bound float32 variants gain little from fewer neighbours, float64
-// issue-bound almost in proportion; measured with one, two and four tiles
-// per split at N = 16384 .. 262144), and each workgroup costs about a tenth
-// of a tile besides.  The reduction reads 68 bytes per i-particle and split
-// at about 4.3 TB/s.
+// workgroups on each compute unit (48 us in double-single, 40 us in float32,
+// 78 us in float64).  Workgroups run in rounds of four per compute unit, and
+// each costs about a tenth of a tile besides.  A single round of k workgroups
+// per compute unit takes the fraction `first` of a full one (latency-bound
+// float32 variants gain little from fewer neighbours, float64 issue-bound
+// almost in proportion; measured with one, two and four tiles per split at N =
+// 16384 .. 262144).  After full rounds the remainder overlaps the last of them
+// (`later`), and a full last round ends with its slowest workgroup, a tenth of
+// a split late (4096 against 2^20 in double-single: 64 splits, one round, 3.43
+// ms; 128, 256, 512 and 1024 splits 3.24, 3.13, 3.12 and 3.16).  The reduction
+// reads 68 bytes per i-particle and split at about 4.3 TB/s.
 int fill_tiles(int prec, int ncu, long ni, long nib, int ntiles) {
-  static const double part32[4] = {0.52, 0.62, 0.87, 1.0}, part64[4] = {0.33, 0.55, 0.85, 1.0};
-  const double *part = prec == G6MI_PREC_FP64 ? part64 : part32;
-  const double tile_us = prec == G6MI_PREC_FP64 ? 88.0 : (prec == G6MI_PREC_DS ? 53.0 : 44.0);
+  static const double first32[4] = {0.52, 0.62, 0.87, 1.0}, later32[4] = {0.38, 0.58, 0.82, 1.0};
+  static const double part64[4] = {0.33, 0.55, 0.85, 1.0};
+  const bool f64 = prec == G6MI_PREC_FP64;
+  const double tile_us = f64 ? 78.0 : (prec == G6MI_PREC_DS ? 48.0 : 40.0);
   const long slots = 4L * ncu;
   int best = 1;
   double least = INFINITY;
   for (int per = 1; per <= std::min(ntiles, 64); ++per) {
     const long nsplit = (ntiles + per - 1) / per;
     if (nsplit > 4096) continue;
-    const long wgs = nib * nsplit, rem = wgs % slots;
-    double t = static_cast<double>(wgs / slots) * (per + 0.1);
-    if (rem > 0) t += per * part[std::min(3L, (rem - 1) / ncu)] + 0.1;
+    const long wgs = nib * nsplit, full = wgs / slots, rem = wgs % slots;
+    const long k = rem > 0 ? std::min(3L, (rem - 1) / ncu) : 3;
+    const double *part = f64 ? part64 : (full > 0 ? later32 : first32);
+    double t = static_cast<double>(full) * (per + 0.1);
+    if (rem > 0) t += per * part[k] + 0.1;
+    if (k == 3) t += std::max(0.0, 0.1 * per - 0.2);
     t += static_cast<double>(nsplit) * ni * 68.0 / (4.3e6 * tile_us);
     if (t < least) {
       least = t;
@@ -437,12 +444,12 @@ int fill_tiles(int prec, int ncu, long ni, long nib, int ntiles) {
 }
 
 // From this many tiles times i-blocks of 256 on, two i-particles per lane
-// are the faster: float64 2^18 x 2^18 73.4 against 75.0 ms (2^20 tiles),
-// 16384 x 2^20 (2^18 tiles) level, 2048 x 2^18 655 against 646 us; double-
-// single 131072 x 2^20 (2^21 tiles) 93.4 against 94.6 ms, 16384 x 2^20 12.2
-// against 11.9 ms.  Float32 with one per lane is faster throughout (131072 x
-// 2^20 76.8 against 78.8 ms, 2048 x 2^18 366 against 407 us).
-constexpr long kWideTiles64 = 1L << 18, kWideTilesDS = 1L << 20;
+// are level or the faster: float64 4096 x 2^20 (2^16 tiles) 4956 against 4986
+// us, 16384 x 2^18 4911 against 4925, but 2048 x 2^20 2519 against 2506;
+// double-single 8192 x 2^20 (2^17 tiles) 6198 against 6248 us, 32768 x 2^20
+// 23.7 against 24.0 ms, but 60000 x 2^17 5735 against 5696 us.  Float32 with
+// one per lane is faster throughout (20000 x 2^20 12.2 against 12.6 ms).
+constexpr long kWideTiles64 = 1L << 16, kWideTilesDS = 1L << 17;
 
 // Spatial ordering (g6mi_spatial.hip) for double-single blocks of at least
 // this many i-particles against at least two tiles (automatic mode).  The
@@ -525,6 +532,8 @@ int piece_tiles(const Handle &h, int ipw, bool one, bool spatial, int ni, int nj
 // against 32768 (256 workgroups) 41 with four sets, 61 with one; 200 against
 // 50000 in float32 (196) 37 and 54; 100 against 100000 (391) 50 with four, 43
 // with two, 46 with one; 400 against 100000 (782) 123 with four, 106 with one.
+// (With the last i-block's rows in its first waves; since they are dealt
+// evenly, first_row, the 341 with four sets take 3.6 us less.)
 int piece_sets(const Handle &h, long nwg) {
   const long ncu = std::max(1, h.ncu);
   return nwg <= ncu ? 4 : (nwg <= 2 * ncu ? 2 : 1);

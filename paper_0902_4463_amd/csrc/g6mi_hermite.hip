@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void hs_publish_kernel(HermiteArgs h, BatchArg
 // use: no neighbour lists, and the nearest neighbour only as far as it
 // decides the float32 sums (fold_or_add; the exact r^2 on splits that end in
 // a ragged tile).  The sums are those of batch_kernel.  Per step of the
-// 32768-particle run 21.0 us, against 24.6 us of batch_kernel and 3.3 us of a
+// 32768-particle run 21.0-21.6 us, against 24.6 us of batch_kernel and 3.3 us of a
 // launch for the plan before it.
 template <int PREC>
 __global__ __launch_bounds__(kWG, wide_waves<PREC>()) void hs_force_kernel(HermiteArgs h, BatchArgs b) {

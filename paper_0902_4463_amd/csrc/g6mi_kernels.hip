@@ -3,10 +3,16 @@
 //   predict_kernel  -- j-particle predictor, Eq. (1)-(2) of Sec. 2.2, in
 //                      float64, writing the predicted j-records in the layout
 //                      of the selected precision variant (HBM-bound).
-//   force_kernel    -- the i x j interaction (Sec. 2.3): LDS-staged j-tiles,
-//                      j-split across workgroups, several lanes per
-//                      i-particle when the block is small, nearest neighbour
-//                      and neighbour lists fused in the same loop (VALU-bound).
+//   force_wide, force_one, force_kernel
+//                   -- the i x j interaction (Sec. 2.3) with two, one or part
+//                      of a lane per i-particle: LDS-staged j-tiles, j-split
+//                      across workgroups, nearest neighbour and neighbour
+//                      lists fused in the same loop (VALU-bound).
+//   piece_min_kernel, force_piece
+//                   -- blocks whose j-splits are too few for the device, in
+//                      pieces of a split (PieceArgs).
+//   force_fused, force_fused_one
+//                   -- one i-block, the predictor fused in.
 //   reduce_kernel   -- fixed-order float64 sum of the j-split partials, the
 //                      nearest-neighbour minimum and the neighbour-list
 //                      finalisation (slot -> particle index, ascending).
@@ -307,7 +313,8 @@ __global__ __launch_bounds__(S * kWG) void piece_min_kernel(ForceArgs a, JMem jm
 // block of a few hundred i-particles against 2^15 records is one workgroup
 // per compute unit: with one set the chains' latency is exposed (341 against
 // 2^15 in double-single: this kernel 38.5 us with one set, 23.9 with four,
-// piece_min_kernel 18.8 and 12.9).
+// piece_min_kernel 18.8 and 12.9; 21.6 and 12.1 since the waves are dealt
+// evenly over the i-blocks, first_row).
 // Grid: x = i-blocks, y = pieces, one split after the other; each starts from
 // the minima of its split's earlier tiles.  The double buffer lets the other
 // sets go on to the next round while set 0 adds.
