@@ -513,13 +513,16 @@ void choose_shape(Handle &h, int ni, int nj, int &ipw, int &nsplit, bool &one, b
 // per compute unit allow.  Measured: 341 i-particles against 2^15 in
 // double-single 258 us of kernels in 16 splits of eight tiles, 57 us in 128
 // pieces of one; with two workgroups per compute unit (100 against 2^20)
-// the minima cost as much as the pieces gain.
+// the minima cost as much as the pieces gain.  Nor do they pay where a split
+// of two tiles is a chain of at most eight groups per lane (17 or 64 against
+// 300: whole 14.1 and 18.6 us per call, pieces 17.1 and 20.3; 100 against 300
+// 28.3 and 26.1, 17 against 600 21.1 and 17.6).
 int piece_tiles(const Handle &h, int ipw, bool one, bool spatial, int ni, int nj, int nsplit) {
   if (spatial || ni <= 0 || nj <= 0 || h.user_ipw || h.user_nsplit || ipw > kWG || free_splits(h.prec, ipw, one))
     return 0;
   const long ncu = std::max(1, h.ncu), nib = (ni + ipw - 1) / ipw, ntiles = (nj + kTile - 1) / kTile;
   const long vper = (ntiles + nsplit - 1) / nsplit;
-  if (nib * nsplit >= 2 * ncu || vper < 2) return 0;
+  if (nib * nsplit >= 2 * ncu || vper < (ipw <= 64 ? 3 : 2)) return 0;
   const long per = (nib * ntiles + 4 * ncu - 1) / (4 * ncu);
   return static_cast<int>(std::min(per, vper));
 }

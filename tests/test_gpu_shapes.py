@@ -87,8 +87,13 @@ def test_pieces_match_whole_splits(prec, n, ni):
         xi, vi = jm.x[slots], jm.v[slots]
         a = evaluate(g6, s, jm, slots, xi, vi, 0.0, 0.02, (0, 0))
         got = g6.g6mi_get_shape(s.id)
-        # one tile per piece; the last split's pieces may be empty
-        assert got["i_per_group"] == ipw and ntiles <= got["j_splits"] < ntiles + max(1, ntiles // 8)
+        # one tile per piece; the last split's pieces may be empty; a split of
+        # two tiles against few i-particles stays whole
+        assert got["i_per_group"] == ipw
+        if ntiles == 2 and ipw <= 64:
+            assert got["j_splits"] == 1
+        else:
+            assert ntiles <= got["j_splits"] < ntiles + max(1, ntiles // 8)
         b = evaluate(g6, s, jm, slots, xi, vi, 0.0, 0.02, (ipw, max(1, ntiles // 8)))
     assert_same_sums(a, b)
 
