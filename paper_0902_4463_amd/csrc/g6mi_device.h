@@ -1085,7 +1085,7 @@ __device__ __forceinline__ void split_sum(int nsplit, int log2I, int nrows, cons
     add(o, __shfl_xor(bs, m));
   }
   const int stride = (4 << log2I) < 64 ? 64 : (4 << log2I); // threads between two parts left
-  if (stride < kWG) {
+  if (stride < kWG && nsplit > 1) { // one split: its sums are in the first part
     sh.v[t] = make_double2(s0, s1);
     sh.sl[t] = bs;
     __syncthreads();
