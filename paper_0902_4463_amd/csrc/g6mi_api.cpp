@@ -425,7 +425,10 @@ int fill_tiles(int prec, int ncu, long ni, long nib, int ntiles) {
   const long slots = 4L * ncu;
   int best = 1;
   double least = INFINITY;
-  for (int per = 1; per <= std::min(ntiles, 64); ++per) {
+  // the split partials stay within 4 GiB (68 bytes per i-particle and split)
+  const long most = std::max(1L, (4L << 30) / (68 * std::max(1L, ni)));
+  const int from = static_cast<int>((ntiles + most - 1) / most);
+  for (int per = from; per <= std::min(ntiles, std::max(from, 64)); ++per) {
     const long nsplit = (ntiles + per - 1) / per;
     if (nsplit > 4096) continue;
     const long wgs = nib * nsplit, full = wgs / slots, rem = wgs % slots;
