@@ -1964,12 +1964,18 @@ int hs_capture(Handle &h, const BatchArgs &b, int steps, hipStream_t s, hipGraph
 }
 
 // Batch arguments of the current block (descriptor in the control block).
+// Block steps make no neighbour lists, whatever the handle's switch says:
+// hs_force_kernel counts no neighbours, so the counters and lists that the
+// reduction would finish are those of an earlier calculation, with entries
+// that are particle indices already.
 int hs_batch(Handle &h, BatchArgs &b) {
   HermiteArgs &a = h.hs.a;
   const int n = h.hs.n;
   int *nnb = reinterpret_cast<int *>(a.pot1 + 2 * static_cast<size_t>(n));
-  return prepare_batch(h, 1, &a.ctl->desc, n, n, a.active, a.xi, a.vi, a.h2i, a.acc1, a.jrk1, a.pot1, nnb,
-                       a.pot1 + n, b);
+  const int rc = prepare_batch(h, 1, &a.ctl->desc, n, n, a.active, a.xi, a.vi, a.h2i, a.acc1, a.jrk1, a.pot1, nnb,
+                               a.pot1 + n, b);
+  b.nbl = 0;
+  return rc;
 }
 
 int hs_read_ctl(Handle &h, hipStream_t s, HermiteCtl &c) {

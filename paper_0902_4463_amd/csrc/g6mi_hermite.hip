@@ -161,7 +161,7 @@ __device__ __forceinline__ BatchPlan plan_block(const g6mi_cluster &d, const Bat
 // First force evaluation: the block's descriptor, plan and work tables for
 // the batched kernels; then the block-time keys turn over (see HermiteCtl).
 __global__ __launch_bounds__(256) void hs_publish_kernel(HermiteArgs h, BatchArgs b) {
-  __shared__ int s_items, s_nib, s_ni;
+  __shared__ int s_items, s_nib;
   if (threadIdx.x == 0) {
     HermiteCtl *ctl = h.ctl;
     const int ph = ctl->phase;
@@ -177,7 +177,6 @@ __global__ __launch_bounds__(256) void hs_publish_kernel(HermiteArgs h, BatchArg
     b.status[kStatusOverflowCount] = 0;
     s_items = min(items, b.item_cap);
     s_nib = pl.nib;
-    s_ni = d.ni;
     // the corrector adds the block's new times to key[ph ^ 1]; the next
     // selection reads it and fills key[ph] afresh
     ctl->ni_count = 0;
@@ -187,8 +186,6 @@ __global__ __launch_bounds__(256) void hs_publish_kernel(HermiteArgs h, BatchArg
   __syncthreads();
   for (int q = threadIdx.x; q < s_items; q += 256) b.item_cl[q] = 0;
   for (int q = threadIdx.x; q < s_nib; q += 256) b.ib_cl[q] = 0;
-  if (b.nbl)
-    for (int r = threadIdx.x; r < s_ni; r += 256) b.fa.nb_count[r] = 0;
 }
 
 // Forces on the block of a step: the items of batch_kernel for a batch of one
