@@ -308,6 +308,9 @@ int ensure_jmem(Handle &h, size_t need) {
   h.jm.index = reinterpret_cast<int *>(b + 14 * cap);
   h.jm.cap = cap;
   HIPCHK(&h, hipMemsetAsync(h.d_jm.p, 0, bytes, h.stream));
+  // the upload that follows may run on a caller's stream, which nothing orders
+  // after the handle's
+  HIPCHK(&h, hipStreamSynchronize(h.stream));
   for (size_t k = 0; k < std::min(h.h_set.size(), cap); ++k)
     if (h.h_set[k]) mark_dirty(h, static_cast<int>(k));
   return 0;
