@@ -791,6 +791,30 @@ struct BlockRows {
       : first(first_row(a, blockIdx.x, gridDim.x)), end(min(a.ni, first_row(a, blockIdx.x + 1, gridDim.x))) {}
 };
 
+// ------------------------------- pieces of j-splits (PieceArgs)
+
+// Tiles [begin, end) of piece y and the first tile of its split: the piece
+// starts from the minima of tiles [split, begin).  A split shorter than vper
+// has trailing pieces without a tile: begin = end = split, no minimum read.
+struct PieceRange {
+  int split, begin, end;
+};
+__host__ __device__ __forceinline__ PieceRange piece_range(const PieceArgs &pc, int ntiles, int y) {
+  const int ppv = (pc.vper + pc.per - 1) / pc.per; // pieces per split
+  PieceRange r;
+  r.split = y / ppv * pc.vper;
+  r.begin = r.split + y % ppv * pc.per;
+  r.end = min(min(ntiles, r.split + pc.vper), r.begin + pc.per);
+  if (r.begin >= r.end) r.begin = r.end = r.split;
+  return r;
+}
+// Whether a later piece of tile tt's split follows the tile's own piece, so
+// that the tile's minima are needed.
+__host__ __device__ __forceinline__ bool piece_follows(const PieceArgs &pc, int ntiles, int tt) {
+  const int pos = tt % pc.vper, len = min(pc.vper, ntiles - (tt - pos)); // place in the split, its tiles
+  return pos / pc.per < (len - 1) / pc.per;
+}
+
 // ------------------------------------- one i-particle on L lanes
 
 // Lane state of a narrow block: ipw i-particles per workgroup (a power of

@@ -156,20 +156,20 @@ __global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a, PieceArgs pc) {
   n.init(a, i, i < rows.end, tid >> a.log2ipw, 8 - a.log2ipw);
   const real_t<PREC> eps2 = static_cast<real_t<PREC>>(a.eps2);
 
+  const bool busy = __any(n.valid); // whole waves without an i-particle have no work
   const int ntiles = (a.nj + kTile - 1) / kTile;
   const float4 *jp = static_cast<const float4 *>(a.jpred);
   int tb, te;
   if constexpr (PIECES) {
-    const int ppv = (pc.vper + pc.per - 1) / pc.per; // pieces per split
-    const int v0 = static_cast<int>(blockIdx.y) / ppv * pc.vper;
-    tb = v0 + static_cast<int>(blockIdx.y) % ppv * pc.per;
-    te = min(min(ntiles, v0 + pc.vper), tb + pc.per);
-    for (int tt = v0; tt < min(tb, te); ++tt) {
+    const PieceRange r = piece_range(pc, ntiles, blockIdx.y);
+    tb = r.begin;
+    te = r.end;
+    for (int tt = r.split; busy && tt < tb; ++tt) {
       const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + tid;
       const float m = pc.least[e];
       if (m < n.gbest) {
         n.gbest = m;
-        if (pc.exact && v0 == pc.vlast) n.ebest = fminf(n.ebest, pc.exact[e]);
+        if (pc.exact && r.split == pc.vlast) n.ebest = fminf(n.ebest, pc.exact[e]);
       }
     }
   } else {
@@ -177,7 +177,6 @@ __global__ __launch_bounds__(kWG) void force_kernel(ForceArgs a, PieceArgs pc) {
     tb = blockIdx.y * per;
     te = min(ntiles, tb + per);
   }
-  const bool busy = __any(n.valid); // whole waves without an i-particle have no work
 
   // The next tile's records are loaded into registers while the current
   // one is evaluated: a block of few i-particles spends little time per
@@ -241,9 +240,7 @@ __global__ __launch_bounds__(S * kWG) void piece_min_kernel(ForceArgs a, JMem jm
     if (lid < a.ipw && valid) a.nb_count[i] = 0;
   }
   const int jbase = tt * kTile, cnt = min(kTile, a.nj - jbase);
-  const int pos = tt % pc.vper;
-  const int len = min(pc.vper, (a.nj + kTile - 1) / kTile - (tt - pos)); // tiles of the split
-  const bool need = pos / pc.per < (len - 1) / pc.per;                   // a later piece follows
+  const bool need = piece_follows(pc, (a.nj + kTile - 1) / kTile, tt);
   if (blockIdx.x > 0 && !need) return;
   if (set == 0 && lid < cnt) {
     predict_record<PREC>(jm, static_cast<size_t>(jbase + lid), ti, tile + lid * REC);
@@ -297,7 +294,7 @@ __global__ __launch_bounds__(S * kWG) void piece_min_kernel(ForceArgs a, JMem jm
   }
   const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + lid;
   pc.least[e] = best;
-  if (pc.exact && tt - pos == pc.vlast) {
+  if (pc.exact && tt >= pc.vlast) {
     float r2 = INFINITY;
     int bs = -1;
     resolve_group<PREC>(st, grp, 1 << log2L, tile, jbase, r2, bs, slot);
@@ -339,21 +336,18 @@ __global__ __launch_bounds__(S * kWG, 4) void force_piece(ForceArgs a, PieceArgs
 
   const int ntiles = (a.nj + kTile - 1) / kTile;
   const float4 *jp = static_cast<const float4 *>(a.jpred);
-  const int ppv = (pc.vper + pc.per - 1) / pc.per; // pieces per split
-  const int v0 = static_cast<int>(blockIdx.y) / ppv * pc.vper;
-  const int tb = v0 + static_cast<int>(blockIdx.y) % ppv * pc.per;
-  const int te = min(min(ntiles, v0 + pc.vper), tb + pc.per);
-  if (set == 0)
-    for (int tt = v0; tt < min(tb, te); ++tt) {
+  const PieceRange range = piece_range(pc, ntiles, blockIdx.y);
+  if (set == 0 && busy)
+    for (int tt = range.split; tt < range.begin; ++tt) {
       const size_t e = (static_cast<size_t>(tt) * gridDim.x + blockIdx.x) * kWG + lid;
       const float m = pc.least[e];
       if (m < n.gbest) {
         n.gbest = m;
-        if (pc.exact && v0 == pc.vlast) n.ebest = fminf(n.ebest, pc.exact[e]);
+        if (pc.exact && range.split == pc.vlast) n.ebest = fminf(n.ebest, pc.exact[e]);
       }
     }
 
-  for (int tt = tb; tt < te; ++tt) {
+  for (int tt = range.begin; tt < range.end; ++tt) {
     const int jbase = tt * kTile;
     const int cnt = min(kTile, a.nj - jbase);
     __syncthreads();
