@@ -1239,7 +1239,7 @@ G6MI_API int g6_close(int id) {
   h->hs.h_rows.release();
   for (DevBuf *b : {&h->d_jm, &h->d_pred, &h->d_stage, &h->d_i, &h->d_out, &h->d_part,
                     &h->d_min, &h->d_nnslot, &h->d_nbcount, &h->d_nblist, &h->d_flags,
-                    &h->d_ovf, &h->d_cl, &h->d_plan, &h->d_items, &h->d_bwork, &h->d_ibcl, &h->d_sp})
+                    &h->d_ovf, &h->d_nbwork, &h->d_cl, &h->d_plan, &h->d_items, &h->d_bwork, &h->d_ibcl, &h->d_sp})
     b->release();
   for (PinBuf *b : {&h->h_stage, &h->h_i, &h->h_out, &h->h_nb, &h->h_cl}) b->release();
   if (h->cl_ev) (void)hipEventDestroy(h->cl_ev);
