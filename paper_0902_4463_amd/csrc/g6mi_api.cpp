@@ -1398,9 +1398,12 @@ G6MI_API int g6_read_neighbour_list(int id) {
   const size_t n = static_cast<size_t>(h->c_ni);
   const ForceArgs &ca = h->c_batch ? h->c_bargs.fa : h->c_args;
   const int *d_status = h->c_batch ? h->c_bargs.status : h->c_flags;
+  // lists off: no neighbours, whatever the counters hold (a batch leaves
+  // those of the calculation before)
+  const bool listed = n > 0 && h->c_nbl;
   // few lists: one kernel writes status words, counts and the stored entries
   // to pinned host memory
-  const bool small = n > 0 && n <= static_cast<size_t>(kPinnedOutNi);
+  const bool small = listed && n <= static_cast<size_t>(kPinnedOutNi);
   const int *out = nullptr;
   int status[kStatusWords] = {0, 0};
   auto fetch = [&]() -> int {
@@ -1416,11 +1419,11 @@ G6MI_API int g6_read_neighbour_list(int id) {
     }
     return 0;
   };
-  if (n > 0) {
+  if (listed) {
     int rc = fetch();
     if (rc) return rc;
     // overflowed lists: keep the G6MI_NB_MAX smallest indices (exact pass)
-    if (h->c_nbl && status[kStatusOverflowCount] > 0 && !h->nb_exact_done) {
+    if (status[kStatusOverflowCount] > 0 && !h->nb_exact_done) {
       if (h->c_batch)
         HIPCHK(h, launch_batch_nb_exact(h->c_prec, h->c_bargs, status[kStatusOverflowCount], h->c_stream));
       else if (h->c_fused)
@@ -1443,7 +1446,9 @@ G6MI_API int g6_read_neighbour_list(int id) {
     for (size_t i = 0; i < n; ++i)
       std::memcpy(&h->r_nblist[i * kNbMax], lists + i * kNbMax,
                   sizeof(int) * static_cast<size_t>(std::max(0, std::min(cnt[i], kNbMax))));
-  } else if (n > 0) {
+  } else if (!listed) {
+    std::fill(h->r_nbcount.begin(), h->r_nbcount.end(), 0);
+  } else {
     HIPCHK(h, hipMemcpy(h->r_nbcount.data(), ca.nb_count, n * sizeof(int), hipMemcpyDeviceToHost));
     HIPCHK(h, hipMemcpy(h->r_nblist.data(), ca.nb_slot, n * kNbMax * sizeof(int), hipMemcpyDeviceToHost));
   }

@@ -1,4 +1,5 @@
-"""What a handle leaves behind: device memory after g6_close."""
+"""What a handle leaves behind and what its switches promise, beside the
+results: device memory after g6_close, neighbour lists switched off."""
 
 import numpy as np
 import pytest
@@ -49,3 +50,43 @@ def test_close_returns_device_memory():
     for _ in range(64):
         last = cycle()
     assert free - last < 64 * 2 ** 15
+
+
+@pytest.mark.parametrize("ni", [300, 1500])
+def test_lists_off_report_no_neighbours(ni):
+    """After calculations with lists on, a calculation with lists off reports
+    zero neighbours: device calls and batches, few and many rows."""
+    import torch
+
+    import paper_0902_4463_amd as g6
+    n, hid = 2000, 4
+    jm = workloads.random_cluster(n, seed=5300)
+    rows = np.arange(ni)
+    dev = _device_inputs(torch, jm, rows, 1.0)
+    out = [torch.zeros(ni, k, dtype=torch.float64, device="cuda") for k in (3, 3, 1)]
+    ti = float(jm.t.max())
+    cl = g6.clusters([0, 0], [n, n], [0, 100], [100, ni - 100], [ti] * 2, [1e-4] * 2)
+
+    def counts(batch):
+        torch.cuda.synchronize()
+        g6.g6_set_ti(hid, ti)
+        if batch:
+            g6.check(hid, g6.g6mi_batch_calc(hid, cl, ni, *dev, *out))
+        else:
+            g6.check(hid, g6.g6mi_calc_device(hid, n, ni, *dev[:3], 1e-4, dev[3], *out))
+        rc = g6.check(hid, g6.g6_read_neighbour_list(hid))
+        ln, buf, got = np.zeros(1, dtype=np.int32), np.zeros(g6.NB_MAX, dtype=np.int32), []
+        for i in range(ni):
+            g6.check(hid, g6.g6_get_neighbour_list(hid, i, g6.NB_MAX, ln, buf))
+            got.append(int(ln[0]))
+        return rc, np.array(got)
+
+    with g6.Session(hid) as s:
+        s.load(jm)
+        for batch in (False, True):
+            g6.check(hid, g6.g6mi_set_neighbour_lists(hid, True))
+            assert (counts(batch)[1] > 0).any()
+            g6.check(hid, g6.g6mi_set_neighbour_lists(hid, False))
+            for other in (batch, not batch):
+                rc, got = counts(other)
+                assert rc == g6.OK and not got.any(), (batch, other)
