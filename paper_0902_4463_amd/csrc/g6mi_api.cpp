@@ -407,6 +407,13 @@ int few_splits(int prec, int ipw) {
   return prec == G6MI_PREC_FP64 && ipw * kGroup > kTile ? 1024 : 512;
 }
 
+// Most bytes of the split partials of force_one (68 per i-particle and split),
+// which a handle keeps: what the widest grid of force_wide takes (64 workgroups
+// of 512 on each of 256 compute units).  More splits gain next to nothing: 2^20
+// i-particles against 2^20 in float32, 606.8 ms with 8 splits (0.5 GiB), 604.4
+// with 60 (4 GiB); 2^18 151.1 with 32, 150.9 with 64 (force_wide 624.9 and 156.6).
+constexpr long kOnePartialBudget = 544L << 20;
+
 // Tiles per split of force_one over nib i-blocks of 256 and ntiles tiles: the
 // choice with the least modelled time, in units of a tile's time with four
 // workgroups on each compute unit (48 us in double-single, 40 us in float32,
@@ -428,8 +435,7 @@ int fill_tiles(int prec, int ncu, long ni, long nib, int ntiles) {
   const long slots = 4L * ncu;
   int best = 1;
   double least = INFINITY;
-  // the split partials stay within 4 GiB (68 bytes per i-particle and split)
-  const long most = std::max(1L, (4L << 30) / (68 * std::max(1L, ni)));
+  const long most = std::max(1L, kOnePartialBudget / (68 * std::max(1L, ni)));
   const int from = static_cast<int>((ntiles + most - 1) / most);
   for (int per = from; per <= std::min(ntiles, std::max(from, 64)); ++per) {
     const long nsplit = (ntiles + per - 1) / per;

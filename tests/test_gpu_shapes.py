@@ -153,3 +153,25 @@ def test_host_calls_with_and_without_copies(ni, changed):
                 jm.index[new] += 5 * 10 ** 8
                 g6.check(s.id, g6.g6mi_set_j_particles(s.id, changed, new, jm.index[new], jm.t[new], None, jm.m[new],
                                                        jm.j6[new], jm.a2[new], jm.v[new], jm.x[new]))
+
+
+def test_partials_of_large_float32_calls():
+    """One i-particle per lane for a large float32 block takes no more memory
+    for its split partials (68 bytes per i-particle and split, kept by the
+    handle) than two per lane on 64 workgroups of 512 per compute unit."""
+    import torch
+
+    import paper_0902_4463_amd as g6
+    n, ni, hid = 1 << 20, 1 << 18, 4
+    x = torch.rand(n, 3, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    z, t = torch.zeros_like(x), torch.zeros(n, dtype=torch.float64, device="cuda")
+    index = torch.arange(n, dtype=torch.int32, device="cuda")
+    out = [torch.zeros(ni, k, dtype=torch.float64, device="cuda") for k in (3, 3, 1)]
+    torch.cuda.synchronize()
+    with g6.Session(hid, precision="fp32", neighbour_lists=False):
+        g6.check(hid, g6.g6mi_set_j_particles_device(hid, n, t, t + 1.0 / n, index, x, z, z, z))
+        g6.check(hid, g6.g6mi_calc_device(hid, n, ni, index, x, z, 1e-6, t, *out))
+        shape, ncu = g6.g6mi_get_shape(hid), g6.g6mi_device_info(hid)["compute_units"]
+        assert g6.g6mi_last_status(hid) == 0
+    assert shape["i_per_group"] == 256
+    assert 68 * ni * shape["j_splits"] <= 68 * 512 * 64 * max(ncu, 256)
