@@ -455,13 +455,20 @@ int fill_tiles(int prec, int ncu, long ni, long nib, int ntiles) {
   return std::isinf(least) ? (ntiles + 4095) / 4096 : best;
 }
 
-// From this many tiles times i-blocks of 256 on, two i-particles per lane
-// are level or the faster: float64 4096 x 2^20 (2^16 tiles) 4956 against 4986
-// us, 16384 x 2^18 4911 against 4925, but 2048 x 2^20 2519 against 2506;
-// double-single 8192 x 2^20 (2^17 tiles) 6198 against 6248 us, 32768 x 2^20
-// 23.7 against 24.0 ms, but 60000 x 2^17 5735 against 5696 us.  Float32 with
-// one per lane is faster throughout (20000 x 2^20 12.2 against 12.6 ms).
-constexpr long kWideTiles64 = 1L << 16, kWideTilesDS = 1L << 17;
+// From this many tiles times i-blocks of 256 on, two i-particles per lane are
+// the faster (medians of seven runs each in turn, which repeat to 0.5% with two
+// per lane and to 1-2% with one; one against two).  Float64: from 2^14 on two
+// per lane gain 1-2% (1024 x 2^20 1.011, 2048 x 2^20 1.017, 3000 x 2^20 1.022,
+// 12000 x 2^18 1.018, 30000 x 2^17 1.015; 4096 x 2^18 0.998 and 30000 x 2^16
+// 0.965 go the other way), below it one per lane does, most where the last
+// workgroup of 512 is partly filled (2^13: 512 x 2^20 1.015, 2048 x 2^18 0.998,
+// 16384 x 2^15 0.981; 3500 x 2^18 0.924, 700 x 2^20 0.780).  Double-single:
+// 8192 x 2^20 and 32768 x 2^18 (2^17 tiles) 1.035 and 1.032, from 2^16 to there
+// level (4096 x 2^20 1.007, 16384 x 2^18 0.998, 24000 x 2^18 0.988, 60000 x 2^17
+// 0.999), below one per lane (2048 x 2^20 0.972, 2048 x 2^18 0.872).  Float32:
+// one per lane throughout (4096 x 2^20 0.946, 8192 x 2^20 0.989, 65536 x 2^20
+// 0.981; 16384 x 2^20 level, 1.004 and 1.03 in two runs).
+constexpr long kWideTiles64 = 1L << 14, kWideTilesDS = 1L << 17;
 
 // Spatial ordering (g6mi_spatial.hip) for double-single blocks of at least
 // this many i-particles against at least two tiles (automatic mode).  The

@@ -175,3 +175,23 @@ def test_partials_of_large_float32_calls():
         assert g6.g6mi_last_status(hid) == 0
     assert shape["i_per_group"] == 256
     assert 68 * ni * shape["j_splits"] <= 68 * 512 * 64 * max(ncu, 256)
+
+
+@pytest.mark.parametrize("n,ni,ipw", [(1 << 18, 4096, 512), ((1 << 18) - 256, 4096, 256), (1 << 14, 1 << 16, 512)])
+def test_float64_blocks_of_many_tiles_take_two_per_lane(n, ni, ipw):
+    """From 2^14 tiles times i-blocks of 256 on."""
+    import torch
+
+    import paper_0902_4463_amd as g6
+    x = torch.rand(max(n, ni), 3, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(6))
+    z, t = torch.zeros_like(x), torch.zeros(len(x), dtype=torch.float64, device="cuda")
+    index = torch.arange(len(x), dtype=torch.int32, device="cuda")
+    out = [torch.zeros(ni, k, dtype=torch.float64, device="cuda") for k in (3, 3, 1)]
+    torch.cuda.synchronize()
+    with g6.Session(4, precision="fp64", neighbour_lists=False):
+        g6.check(4, g6.g6mi_set_j_particles_device(4, n, t, t + 1.0 / n, index, x, z, z, z))
+        slot = torch.where(index < n, index, torch.full_like(index, -1))
+        torch.cuda.synchronize()
+        g6.check(4, g6.g6mi_calc_device(4, n, ni, slot, x, z, 1e-6, t, *out))
+        assert g6.g6mi_last_status(4) == 0
+        assert g6.g6mi_get_shape(4)["i_per_group"] == ipw
