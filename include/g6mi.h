@@ -247,7 +247,11 @@ int g6mi_set_spatial(int id, int mode);
  * Eq. (1)-(2), fused into the tile load) instead of reading records written
  * by a separate predictor launch, so the predicted records never go
  * through HBM.  The arithmetic is the same either way and so are the
- * results, bit for bit.  on = 0 always runs the separate predictor.
+ * results, bit for bit.  Double-single and float32 blocks of 17 particles and
+ * more against too few j-slots to fill the device run in pieces of their
+ * j-splits instead, after one launch that predicts the records and prepares
+ * the pieces, whatever the switch says; otherwise on = 0 runs the separate
+ * predictor.
  * Returns 0, G6MI_EINVAL or G6MI_ESTATE. */
 int g6mi_set_fused_predict(int id, int on);
 
@@ -459,15 +463,18 @@ int g6mi_batch_autotune(int id, int ncl, const g6mi_cluster *cl,
  * Scheme (the 4th-order Hermite integrator with block steps that the
  * paper's library serves, Sec. 2): block time t_b = min(t_k + dt_k); the
  * particles with t_k + dt_k = t_b are predicted to t_b (Eq. (1)-(2) with
- * their own a and jerk) and get new forces from the batched kernels with
- * softening eps2 and neighbour radius^2 h2; the Makino-Aarseth corrector
+ * their own a and jerk) and get new forces with softening eps2, the sums of
+ * a batch of one cluster; the Makino-Aarseth corrector
  * gives x, v at t_b; the next step is Aarseth's sqrt(eta (|a||a2| + |j|^2) /
  * (|j||a3| + |a2|^2)) with a2 taken at the end of the step, halved while
  * too long but never below dt_min, and doubled (up to dt_max) only when t_b is a
  * multiple of the doubled step; the first step is eta_s |a| / |j| rounded
  * down to a power of two in [dt_min, dt_max].
  *
- * g6mi_hermite_init computes the first forces and steps.  Returns 0, 1 if a
+ * g6mi_hermite_init computes the first forces and steps.  Block steps make
+ * no neighbour lists, whatever g6mi_set_neighbour_lists says, and after them
+ * none can be read until the next calculation: h2, a neighbour radius^2, must
+ * be finite and has no effect.  Returns 0, 1 if a
  * force was not finite, or a negative code (G6MI_EINVAL: n larger than the
  * slots set, unequal times, bad parameters).
  *

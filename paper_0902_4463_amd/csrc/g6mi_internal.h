@@ -342,7 +342,7 @@ struct HermiteArgs {
   int n = 0;
   int *active = nullptr;                  // [n] slots of the block, in selection order
   double *xi = nullptr, *vi = nullptr;    // [n][3] block predicted to the block time
-  double *h2i = nullptr;                  // [n]
+  double *h2i = nullptr;                  // [n] radii the force kernels load with a row (unused: no lists)
   double *acc1 = nullptr, *jrk1 = nullptr, *pot1 = nullptr; // [n][3], [n][3], [n] new forces
   double eps2 = 0, h2 = 0, eta = 0, eta_s = 0, dt_max = 0, dt_min = 0;
 };

@@ -314,7 +314,9 @@ __global__ __launch_bounds__(S * kWG) void piece_min_kernel(ForceArgs a, JMem jm
 // evenly over the i-blocks, first_row).
 // Grid: x = i-blocks, y = pieces, one split after the other; each starts from
 // the minima of its split's earlier tiles.  The double buffer lets the other
-// sets go on to the next round while set 0 adds.
+// sets go on to the next round while set 0 adds.  Which sums a group goes to
+// follows NarrowLane::grouped for full tiles and MaskedRun for ragged ones: a
+// change to either rule has to be made here too, or the bits part.
 template <int PREC, bool NBL, int S>
 __global__ __launch_bounds__(S * kWG, 4) void force_piece(ForceArgs a, PieceArgs pc) {
   constexpr int REC = rec4<PREC>();
