@@ -145,10 +145,12 @@ def _pd(a):
     read-only and strided arrays refuse; 1.4 us through a.ctypes)."""
     if a is None:
         return None
-    try:
-        return ctypes.addressof(ctypes.c_char.from_buffer(a))
-    except (TypeError, ValueError, BufferError):
-        return a.ctypes.data
+    if isinstance(a, np.ndarray):
+        try:
+            return ctypes.addressof(ctypes.c_char.from_buffer(a))
+        except (TypeError, ValueError, BufferError):
+            pass
+    return a.ctypes.data  # other objects have no such attribute
 
 
 _pi = _pd
