@@ -123,7 +123,6 @@ __global__ __launch_bounds__(256) void hs_select_kernel(HermiteArgs h) {
       h.xi[3 * static_cast<size_t>(q) + d] = xp[d];
       h.vi[3 * static_cast<size_t>(q) + d] = vp[d];
     }
-    h.h2i[q] = h.h2;
   }
 }
 
@@ -458,6 +457,7 @@ __global__ __launch_bounds__(256) void hs_reset_kernel(HermiteArgs h) {
   if (k >= h.n) return;
   const size_t cap = h.jm.cap;
   h.dt[k] = 0.0;
+  h.h2i[k] = h.h2; // rows 0 .. n-1, for every block
   for (int d = 0; d < 3; ++d) {
     h.acc[d * cap + k] = 0.0;
     h.jrk[d * cap + k] = 0.0;
